@@ -13,9 +13,9 @@
 //  2. Candidate test, 64 candidates per step: separation in FP64 exactly as the
 //     definition orders it (x_j - x_i, then the periodic image), r^2 =
 //     (dx*dx + dy*dy) + dz*dz without contraction, bin by comparing r^2 with the
-//     squared edges.  Accepted pairs are pushed into one LDS ring per bin (slots
+//     squared edges.  Accepted pairs are pushed onto one LDS stack per bin (slots
 //     from lane-mask ballots and mbcnt ranks, no atomics).
-//  3. Drain: whenever a ring holds 64 pairs, all 64 lanes pop one pair each, form
+//  3. Drain: whenever a stack holds 64 pairs, all 64 lanes pop one pair each, form
 //     Y_lm by the monic Legendre recurrence in z times (x + i y)^m and add w Y into
 //     per-lane register accumulators of that bin (the bin is wave-uniform, so the
 //     register index is static).
@@ -43,7 +43,7 @@ namespace encore {
 
 namespace {
 
-constexpr int kCap = 128;          // ring capacity per bin (pairs)
+constexpr int kCap = 128;          // stack capacity per bin (pairs): at most 63 left over plus a chunk
 constexpr int kRowsPerBatch = 64;  // rows set up per lane-parallel pass
 constexpr int kSegPerRow = 6;      // <= 2 x-ranges x 3 periodic images
 constexpr int kSegCap = kRowsPerBatch * kSegPerRow;
@@ -157,7 +157,7 @@ __device__ __forceinline__ void accum_pair(T dx, T dy, T dz, T w, AccT<T, COMP> 
     const T r2 = dx * dx + dy * dy + dz * dz;
     const T inv = rsqrt_t<T>(r2);
     const T x = dx * inv, y = dy * inv, z = dz * inv;
-    const T zw = z * w;
+    const T zw = z * w, zzw = z * zw;
     T ur = (T)1, ui = (T)0;
 #pragma unroll
     for (int m = 1; m <= M0; ++m) {   // (x + i y)^M0
@@ -192,7 +192,8 @@ __device__ __forceinline__ void accum_pair(T dx, T dy, T dz, T w, AccT<T, COMP> 
             if (m + 1 <= L) put(m + 1, r1);
 #pragma unroll
             for (int l = m + 2; l <= L; ++l) {
-                const T rn = z * r1 - (T)Gamma<L>::t.v[lm_index(l, m)] * r0;
+                // the first product, z * zw, is the same for every m
+                const T rn = (l == m + 2 ? zzw : z * r1) - (T)Gamma<L>::t.v[lm_index(l, m)] * r0;
                 put(l, rn);
                 r0 = r1; r1 = rn;
             }
@@ -210,7 +211,7 @@ __device__ __forceinline__ void accum_pair(T dx, T dy, T dz, T w, AccT<T, COMP> 
             }
 #pragma unroll
             for (int l = m + 2; l <= L; ++l) {
-                const T rn = z * r1 - (T)Gamma<L>::t.v[lm_index(l, m)] * r0;
+                const T rn = (l == m + 2 ? zzw : z * r1) - (T)Gamma<L>::t.v[lm_index(l, m)] * r0;
                 if (m == 0) {
                     acc[lm_index(l, 0)][0] += rn;
                 } else {
@@ -257,6 +258,18 @@ __device__ __forceinline__ double uni(double v)
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)u);
     const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(u >> 32));
     return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+
+// Bin group of the quad at position `pos` of row block `rblk`: the positions rotated
+// by a hash of the block.  Without it the groups repeat with the period of the quads,
+// and where that shares a factor with the number of shader engines of an XCD (four;
+// blocks are dealt to them in turn) some engines get all the outermost, heaviest
+// bins: at lmax 4 over 200k points a launch of 4 groups (3 bins per item) took 22.8
+// ms and one of 2 groups (5 bins) 24.8 ms; rotated 14.6 and 16.3 ms.
+__device__ __forceinline__ int bin_group(int pos, unsigned rblk, int ngroups)
+{
+    const unsigned h = (rblk * 0x9E3779B1u) >> 16;
+    return (int)(((unsigned)pos + h) % (unsigned)ngroups);
 }
 
 template <typename PT>
@@ -520,7 +533,7 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
     const int64_t quad = item / kWavesPerBlock;
     // 32-bit division when the quads fit (always, below 2^31 work items)
     const int64_t rblk = quad <= INT32_MAX ? (int64_t)((unsigned)quad / (unsigned)a.ngroups) : quad / a.ngroups;
-    const int grp = uni((int)(quad - rblk * a.ngroups));
+    const int grp = uni(bin_group((int)(quad - rblk * a.ngroups), (unsigned)rblk, a.ngroups));
     const int row = uni((int)(rblk * kWavesPerBlock + (item - quad * kWavesPerBlock)));
     if (row >= a.nrows) return;   // ragged last row block
     // segment (catalog) of this row: binary search over the segments' first rows
@@ -538,20 +551,22 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
     const double xi = uni(Pi.x), yi = uni(Pi.y), zi = uni(Pi.z);
     const int b_lo = grp * NBG;
     const int b_hi = min(b_lo + NBG, a.nbins);
-    const double R2in = uni(a.e2[b_lo]), R2out = uni(a.e2[b_hi]);
-    // interior squared edges of the group (+inf past the last bin of the group)
-    double e2k[NBG];
+    // squared edges of the group's bins (the last edge again past its last bin, so
+    // that the missing bins of a ragged group are empty)
+    double eg[NBG + 1];
 #pragma unroll
-    for (int q = 1; q < NBG; ++q) e2k[q] = uni((b_lo + q < b_hi) ? a.e2[min(b_lo + q, kMaxBins)] : INFINITY);
+    for (int q = 0; q <= NBG; ++q) eg[q] = uni(a.e2[min(b_lo + q, b_hi)]);
     // periodic images: shift per axis for image codes 0, 1, 2 (-L, 0, +L)
     const double Lx = g.Lx, Ly = g.Ly, Lz = g.Lz;
     // culling uses slightly enlarged cells and radius; the bin test below is exact
     const double Rin = uni(a.e1[b_lo]), Rout = uni(a.e1[b_hi]);
     const double Rc = Rout + g.cull_pad;
 
-    int head[NBG], tail[NBG];
+    // pairs held by each bin's stack, as the slot of its next push, and all accepted
+    int top[NBG];
+    unsigned pairs = 0;
 #pragma unroll
-    for (int k = 0; k < NBG; ++k) { head[k] = 0; tail[k] = 0; }
+    for (int k = 0; k < NBG; ++k) top[k] = k * kCap;
     using A = AccT<T, COMP>;
     A acc[NBG][NLM][2];
 #pragma unroll
@@ -695,77 +710,42 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
                     dz = sep(dz, 0.0, (double)(((code >> 4) & 3) - 1) * Lz);
                 }
                 const double r2 = dist2(dx, dy, dz);
-                bool ok;
-                int k = 0;
-                int slot;
-                if constexpr (NBG == 2) {
-                    // three compares give the lane masks: inside the shell, and past
-                    // the interior edge (bin 1); each bin's lanes are ranked by one
-                    // mbcnt of that bin's mask, offset by the bin's tail
-                    const bool c_in = r2 >= R2in, c_out = r2 < R2out, c_k = r2 >= e2k[1];
-                    ok = c_in && c_out;
-                    const unsigned long long okm =
-                        __builtin_amdgcn_ballot_w64(c_in) & __builtin_amdgcn_ballot_w64(c_out);
-                    const unsigned long long km = __builtin_amdgcn_ballot_w64(c_k);
-                    const unsigned long long m1 = okm & km, m0 = okm & ~km;
-                    const unsigned r0 = __builtin_amdgcn_mbcnt_hi((unsigned)(m0 >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)m0, 0u)) +
-                                        (unsigned)tail[0];
-                    const unsigned r1 = __builtin_amdgcn_mbcnt_hi((unsigned)(m1 >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)m1, 0u)) +
-                                        (unsigned)tail[1];
-                    // select by the lane mask itself (both ranks are computed anyway; a
-                    // conditional would be turned into two divergent branches)
-                    const unsigned s0 = r0 & (kCap - 1), s1 = (r1 & (kCap - 1)) | (unsigned)kCap;
-                    unsigned sl;
-                    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(sl) : "v"(s0), "v"(s1), "s"(km));
-                    // rejected lanes write their own dump entry: the ring push then
-                    // needs no exec-mask branch
-                    slot = ok ? (int)sl : NBG * kCap + lane;
-                    tail[0] += __popcll(m0);
-                    tail[1] += __popcll(m1);
-                } else {
-                    ok = (r2 >= R2in) && (r2 < R2out);
-#pragma unroll
-                    for (int q2 = 1; q2 < NBG; ++q2) k += (r2 >= e2k[q2]) ? 1 : 0;
-                    // ring slots: one ballot per bit of the bin index; the lanes of
-                    // the same bin are those agreeing on every bit
-                    constexpr int NBITS = (NBG <= 1) ? 0 : (NBG <= 4) ? 2 : (NBG <= 8) ? 3 : 4;
-                    const unsigned long long okm = __builtin_amdgcn_ballot_w64(ok);
-                    unsigned long long bm[NBITS > 0 ? NBITS : 1];
-                    unsigned long long same = okm;
-#pragma unroll
-                    for (int bb = 0; bb < NBITS; ++bb) {
-                        bm[bb] = __builtin_amdgcn_ballot_w64(ok && ((k >> bb) & 1));
-                        same &= ((k >> bb) & 1) ? bm[bb] : ~bm[bb];
-                    }
-                    const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32),
-                                                               __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
-                    int tk = tail[0];
-#pragma unroll
-                    for (int q2 = 1; q2 < NBG; ++q2) tk = (k == q2) ? tail[q2] : tk;
-#pragma unroll
-                    for (int q2 = 0; q2 < NBG; ++q2) {
-                        unsigned long long mq = okm;
-#pragma unroll
-                        for (int bb = 0; bb < NBITS; ++bb) mq &= ((q2 >> bb) & 1) ? bm[bb] : ~bm[bb];
-                        tail[q2] += __popcll(mq);
-                    }
-                    slot = k * kCap + ((tk + rank) & (kCap - 1));
-                }
+                // One compare per edge of the group gives the lane masks "past edge q";
+                // a bin's lanes are those past its lower and not past its upper edge.
+                // They are ranked by one mbcnt of that mask above the bin's top, and the
+                // slot is selected by the mask itself (a conditional would be turned into
+                // divergent branches).  Lanes of no bin write a dump entry of their own,
+                // so the push needs no exec-mask branch.  A stack and not a ring: the
+                // slot is the rank plus the top, with no wrap to mask off.
+                unsigned slot = (unsigned)(NBG * kCap + lane);
+                unsigned long long past = __builtin_amdgcn_ballot_w64(r2 >= eg[0]);
+                [&]<int... Q>(std::integer_sequence<int, Q...>) {
+                    ([&] {
+                        const unsigned long long up = __builtin_amdgcn_ballot_w64(r2 >= eg[Q + 1]);
+                        const unsigned long long mq = past & ~up;
+                        past = up;
+                        const unsigned sq = __builtin_amdgcn_mbcnt_hi((unsigned)(mq >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((unsigned)mq, 0u)) +
+                                            (unsigned)top[Q];
+                        unsigned sel;
+                        asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(sel) : "v"(slot), "v"(sq), "s"(mq));
+                        slot = sel;
+                        top[Q] += __popcll(mq);
+                    }(), ...);
+                }(std::make_integer_sequence<int, NBG>{});
                 {
                     E ev;
                     ev.x = (T)dx; ev.y = (T)dy; ev.z = (T)dz; ev.w = (T)q.w;
-                    if constexpr (NBG == 2) ring[slot] = ev;
-                    else if (ok) ring[slot] = ev;
+                    ring[slot] = ev;
                 }
                 [&]<int... K>(std::integer_sequence<int, K...>) {
                     ([&] {
-                        if (tail[K] - head[K] >= kWave) {
+                        if (top[K] >= K * kCap + kWave) {
                             wave_sync();
-                            const E e = ring[K * kCap + ((head[K] + lane) & (kCap - 1))];
+                            top[K] -= kWave;
+                            pairs += kWave;
+                            const E e = ring[top[K] + lane];
                             accum_pair<T, L, M0, M1, COMP>(e.x, e.y, e.z, e.w, acc[K]);
-                            head[K] += kWave;
                         }
                     }(), ...);
                 }(std::make_integer_sequence<int, NBG>{});
@@ -789,19 +769,19 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
     }
 
     if (a.npairs && lane == 0) {
-        unsigned long long tot = 0;
+        unsigned long long tot = pairs;
 #pragma unroll
-        for (int k = 0; k < NBG; ++k) tot += (unsigned long long)tail[k];
+        for (int k = 0; k < NBG; ++k) tot += (unsigned long long)(top[k] - k * kCap);
         atomicAdd(a.npairs, tot);
     }
 
-    // ---- flush partial rings (missing lanes add zero-weight pairs)
+    // ---- flush partial stacks (missing lanes add zero-weight pairs)
     wave_sync();
     [&]<int... K>(std::integer_sequence<int, K...>) {
         ([&] {
-            const int rem = tail[K] - head[K];
+            const int rem = top[K] - K * kCap;
             if (rem > 0) {
-                E e = ring[K * kCap + ((head[K] + lane) & (kCap - 1))];
+                E e = ring[K * kCap + lane];
                 if (lane >= rem) { e.x = (T)1; e.y = (T)0; e.z = (T)0; e.w = (T)0; }
                 accum_pair<T, L, M0, M1, COMP>(e.x, e.y, e.z, e.w, acc[K]);
             }
@@ -963,10 +943,16 @@ KernelCfg cfg2()
     return c;
 }
 
-// Bins per work item: fewer bins per item means more passes over the candidates
-// but fewer accumulator registers, hence more resident waves to hide the LDS and
-// L2 latency of the candidate stream.  Several values are compiled for the common
-// cases; encore_autotune picks one per job shape (ENCORE_GATHER_NBG overrides).
+// Bins per work item: more bins per item mean fewer passes over the candidates and
+// fewer row set-ups, but more accumulator registers and LDS stacks, hence fewer
+// resident waves, and one more compare, rank and select per candidate.  Two bins are
+// best or within 3% of best wherever their accumulators fit (4PCF gather, 200k
+// points at the benchmark density / 50k primaries of the survey wedge, ms: lmax 3
+// FP32 2 bins 12.4 / 5.8, 3 bins 13.4 / 6.8, 4 bins 12.7 / 6.5; lmax 4 FP32 2 bins
+// 12.3 / 6.2, 3 bins 14.6 / 7.3; FP64 lmax 3 2 bins 16.7, 5 bins 33.5, lmax 4 2 bins
+// 18.3, 3 bins 24.3); at lmax 0 and 1 four bins win without clustering (11.3 against
+// 12.2) and lose on the wedge (5.8 against 5.1), so both are compiled and
+// encore_autotune picks one per job shape (ENCORE_GATHER_NBG overrides).
 int nbg_env()
 {
     static int v = [] {
@@ -984,11 +970,11 @@ KernelCfg config(int lmax, int precision, int nbg)
     if (nbg_env() > 0) nbg = nbg_env();
     if (precision == 2) {
         switch (lmax) {
-        case 0: return cfg1<float, 0, 8, true>();
-        case 1: return cfg1<float, 1, 8, true>();
-        case 2: return cfg1<float, 2, 8, true>();
-        case 3: return nbg == 2 ? cfg1<float, 3, 2, true>() : cfg1<float, 3, 5, true>();
-        case 4: return nbg == 2 ? cfg1<float, 4, 2, true>() : cfg1<float, 4, 3, true>();
+        case 0: return nbg == 4 ? cfg1<float, 0, 4, true>() : cfg1<float, 0, 2, true>();
+        case 1: return nbg == 4 ? cfg1<float, 1, 4, true>() : cfg1<float, 1, 2, true>();
+        case 2: return cfg1<float, 2, 2, true>();
+        case 3: return cfg1<float, 3, 2, true>();
+        case 4: return cfg1<float, 4, 2, true>();
         case 5: return nbg == 1 ? cfg1<float, 5, 1, true>() : cfg1<float, 5, 2, true>();
         case 6: return cfg1<float, 6, 1, true>();
         case 7: return cfg1<float, 7, 1, true>();
@@ -998,13 +984,13 @@ KernelCfg config(int lmax, int precision, int nbg)
         }
     } else if (precision == 1) {
         switch (lmax) {
-        case 0: return cfg1<float, 0, 16>();
-        case 1: return cfg1<float, 1, 16>();
-        case 2: return nbg == 10 ? cfg1<float, 2, 10>() : cfg1<float, 2, 6>();
-        case 3: return nbg == 5 ? cfg1<float, 3, 5>() : (nbg == 2 ? cfg1<float, 3, 2>() : cfg1<float, 3, 4>());
-        case 4: return nbg == 5 ? cfg1<float, 4, 5>() : (nbg == 2 ? cfg1<float, 4, 2>() : cfg1<float, 4, 3>());
-        case 5: return nbg == 3 ? cfg1<float, 5, 3>() : cfg1<float, 5, 2>();
-        case 6: return nbg == 1 ? cfg1<float, 6, 1>() : cfg1<float, 6, 2>();
+        case 0: return nbg == 4 ? cfg1<float, 0, 4>() : cfg1<float, 0, 2>();
+        case 1: return nbg == 4 ? cfg1<float, 1, 4>() : cfg1<float, 1, 2>();
+        case 2: return cfg1<float, 2, 2>();
+        case 3: return cfg1<float, 3, 2>();
+        case 4: return cfg1<float, 4, 2>();
+        case 5: return cfg1<float, 5, 2>();
+        case 6: return cfg1<float, 6, 2>();
         case 7: return cfg1<float, 7, 1>();
         case 8: return cfg1<float, 8, 1>();
         case 9: return cfg1<float, 9, 1>();
@@ -1012,11 +998,11 @@ KernelCfg config(int lmax, int precision, int nbg)
         }
     } else {
         switch (lmax) {
-        case 0: return cfg1<double, 0, 8>();
-        case 1: return cfg1<double, 1, 8>();
-        case 2: return cfg1<double, 2, 8>();
-        case 3: return nbg == 2 ? cfg1<double, 3, 2>() : cfg1<double, 3, 5>();
-        case 4: return nbg == 2 ? cfg1<double, 4, 2>() : cfg1<double, 4, 3>();
+        case 0: return cfg1<double, 0, 2>();
+        case 1: return cfg1<double, 1, 2>();
+        case 2: return cfg1<double, 2, 2>();
+        case 3: return cfg1<double, 3, 2>();
+        case 4: return cfg1<double, 4, 2>();
         case 5: return cfg1<double, 5, 2>();
         case 6: return cfg1<double, 6, 1>();
         case 7: return cfg1<double, 7, 1>();
@@ -1034,10 +1020,9 @@ int gather_group_bins(int lmax, int precision, int nbg) { return config(lmax, pr
 
 std::vector<int> gather_nbg_options(int lmax, int precision)
 {
-    static const std::vector<int> f32[11] = {{16}, {16}, {6, 10}, {4, 2, 5}, {3, 2, 5}, {2, 3},
-                                             {2, 1}, {1}, {1}, {1}, {1}};
-    static const std::vector<int> f64[11] = {{8}, {8}, {8}, {5, 2}, {3, 2}, {2}, {1}, {1}, {1}, {1}, {1}};
-    static const std::vector<int> f32c[11] = {{8}, {8}, {8}, {5, 2}, {3, 2}, {2, 1}, {1}, {1}, {1}, {1}, {1}};
+    static const std::vector<int> f32[11] = {{2, 4}, {2, 4}, {2}, {2}, {2}, {2}, {2}, {1}, {1}, {1}, {1}};
+    static const std::vector<int> f64[11] = {{2}, {2}, {2}, {2}, {2}, {2}, {1}, {1}, {1}, {1}, {1}};
+    static const std::vector<int> f32c[11] = {{2, 4}, {2, 4}, {2}, {2}, {2}, {2, 1}, {1}, {1}, {1}, {1}, {1}};
     if (lmax < 0 || lmax > 10) return {};
     return precision == 1 ? f32[lmax] : (precision == 2 ? f32c[lmax] : f64[lmax]);
 }
