@@ -183,26 +183,37 @@ int launch_couple_mfma(const MfmaArgs& a, int KF, int shape, hipStream_t stream)
 // and columns, jobs its macro tiles (njobs of them), KL + KR factors.
 int launch_couple_gemm(const MfmaArgs& a, int KL, int KR, hipStream_t stream);
 
-// Edge correction (one workgroup per bin tuple B): builds the coupling matrix from
-// the Gaunt terms and the random multiplets, solves for zeta (NaN for B with R_0 = 0
-// or a singular matrix, counted in *nbad).
-// Largest multiplet count of the edge-correction solve (its factor column sits in LDS).
+// Edge correction: builds the coupling matrices of bin tuples [B_lo, B_lo + nb) from
+// the Gaunt terms and the random multiplets and solves for zeta (NaN for B with R_0 =
+// 0 or a singular matrix, counted in *nbad).
+// Largest multiplet count of the edge-correction solve (four rows per thread of its
+// panels, 16-bit L' in the term lists).
 constexpr int kEdgeMaxMultiplets = 4096;
 struct EdgeArgs {
-    int nlam, nB, nout;
+    int nlam, nB, nout, ld;     // ld: row stride of A, edge_ld(nlam)
     const double* nmult;        // [nlam][nB] data-minus-random multiplets
     const double* rmult;        // [nlam][nB] random multiplets (row 0: L = 0)
-    const int64_t* row_start;   // [nlam * nlam + 1] terms of entry (L, L'')
-    const int32_t* term_lp;     // L'
-    const double* term_val;     // E(L'') G^{L L' L''}
-    double* A;                  // workspace [nB][nlam][nlam]
-    double* rhs;                // workspace [nB][nlam]
+    const int64_t* ell_off;     // terms of the entries (L'', 64 L) (launch_edge_ell)
+    const uint16_t* ell_lp;     // L'
+    const double* ell_val;      // E(L'') G^{L L' L''}
+    double* A;                  // workspace, edge_matrix_bytes
+    double* P;                  // workspace, edge_panel_bytes
+    int32_t* perm;              // workspace, edge_perm_bytes
     const int32_t* keep;        // [nout] output multiplets (indices into the list)
     double* zeta;               // [nout][nB]
     double* M_out;              // optional [nB][nlam][nlam], M[L][L'']
     unsigned* nbad;             // += number of B without a solution
 };
-int launch_edge(const EdgeArgs& a, hipStream_t stream);
+int edge_ld(int n);
+size_t edge_matrix_bytes(int n, int nb);   // of nb systems
+size_t edge_panel_bytes(int n, int nb);
+size_t edge_perm_bytes(int nb);
+int launch_edge(const EdgeArgs& a, int B_lo, int nb, hipStream_t stream);
+// The terms of entry (L, L''), row_start[L n + L''] .. row_start[L n + L'' + 1), as padded
+// blocks: unit L'' ceil(n / 64) + L / 64 spans [ell_off[unit], ell_off[unit + 1]), term t
+// of L % 64 at ell_off[unit] + 64 t + L % 64 (empty where L / 64 < L'' / 64).
+int launch_edge_ell(int n, const int64_t* row_start, const int32_t* term_lp, const double* term_val,
+                    const int64_t* ell_off, uint16_t* lp, double* val, hipStream_t stream);
 // Row-major FP32 coefficients ([nrows][nent] complex) and weights -> blocked layout
 // (out: ceil(nrows / 16) blocks); rows outside every segment's [row0, row0 + nprim)
 // and past nrows become zero with weight zero.

@@ -77,61 +77,88 @@ extern "C" int encore_edge_correct(encore_ctx* ctx, int npcf, int lmax, int nbin
     a.nlam = n;
     a.nB = (int)nB;
     a.nout = nout;
+    a.ld = edge_ld(n);
     int rc;
+    // The systems are solved together, as many at once as fit 32 GiB (all of them at
+    // the sizes of the paper's analyses; at 4096 multiplets 251, about one per CU).
+    const int64_t per_b = (int64_t)edge_matrix_bytes(n, 2) - (int64_t)edge_matrix_bytes(n, 1);
+    const int64_t chunk = std::min<int64_t>(nB, std::max<int64_t>(1, ((int64_t)32 << 30) / per_b));
     // Workspaces: the context's grow-only buffers, kept for later calls; the Gaunt
     // table is uploaded once per (npcf, lmax, parity) while its buffer stays put.
-    const size_t nt = gt.term_lp.size(), nrs = gt.row_start.size();
-    size_t go = 0;
-    const size_t o_rs = carve(go, sizeof(int64_t) * nrs), o_lp = carve(go, sizeof(int32_t) * nt),
-                 o_v = carve(go, sizeof(double) * nt);
-    const size_t gt_n0 = x.egt.n;
-    if ((rc = ensure(x.egt, go))) return rc;
     const auto gt_key = std::make_tuple(npcf, lmax, allp);
-    const bool gt_fresh = ctx->edge_gt_key != gt_key || x.egt.n != gt_n0;
+    const size_t nt = gt.term_lp.size(), nrs = gt.row_start.size();
+    const int64_t nblk = (n + kWave - 1) / kWave;
+    std::vector<int64_t> off;
+    bool gt_fresh = ctx->edge_gt_key != gt_key || !x.egt.p;
+    if (gt_fresh) {
+        // padded lengths of the term lists of (L'', 64 L), on and above the diagonal
+        off.assign((size_t)(n * nblk) + 1, 0);
+        for (int64_t lpp = 0; lpp < n; ++lpp)
+            for (int64_t k = 0; k < nblk; ++k) {
+                int64_t w = 0;
+                for (int64_t L = k < lpp / kWave ? n : k * kWave; L < std::min<int64_t>(n, (k + 1) * kWave); ++L)
+                    w = std::max(w, gt.row_start[L * n + lpp + 1] - gt.row_start[L * n + lpp]);
+                off[lpp * nblk + k + 1] = off[lpp * nblk + k] + w * kWave;
+            }
+        ctx->edge_gt_key = std::make_tuple(-1, -1, false);
+        ctx->edge_ell_len = off.back();
+    }
+    size_t go = 0;
+    const size_t o_off = carve(go, sizeof(int64_t) * (size_t)(n * nblk + 1)),
+                 o_lp = carve(go, sizeof(uint16_t) * (size_t)ctx->edge_ell_len),
+                 o_v = carve(go, sizeof(double) * (size_t)ctx->edge_ell_len);
+    if ((rc = ensure(x.egt, go))) return rc;
     size_t io = 0;
     const size_t o_n = carve(io, sizeof(double) * n * nB), o_r = carve(io, sizeof(double) * n * nB),
-                 o_x = carve(io, sizeof(double) * nB * n), o_k = carve(io, sizeof(int32_t) * nout),
-                 o_z = carve(io, sizeof(double) * nout * nB), o_bad = carve(io, sizeof(unsigned));
-    if ((rc = ensure(x.eio, io)) || (rc = ensure(x.eA, sizeof(double) * nB * n * n))) return rc;
+                 o_k = carve(io, sizeof(int32_t) * nout), o_z = carve(io, sizeof(double) * nout * nB),
+                 o_bad = carve(io, sizeof(unsigned)), o_perm = carve(io, edge_perm_bytes((int)chunk));
+    if ((rc = ensure(x.eio, io))) return rc;
+    // the matrices and the panels; before them, the term lists as uploaded
+    size_t ao = 0, to = 0;
+    const size_t o_A = carve(ao, edge_matrix_bytes(n, (int)chunk)), o_P = carve(ao, edge_panel_bytes(n, (int)chunk));
+    const size_t o_rs = carve(to, sizeof(int64_t) * nrs), o_tl = carve(to, sizeof(int32_t) * nt),
+                 o_tv = carve(to, sizeof(double) * nt);
+    if ((rc = ensure(x.eA, gt_fresh ? std::max(ao, to) : ao))) return rc;
     if (coupling && (rc = ensure(x.eM, sizeof(double) * nB * n * n))) return rc;
     char* gb = (char*)x.egt.p;
     char* ib = (char*)x.eio.p;
-    int64_t* drs = (int64_t*)(gb + o_rs);
-    int32_t* dlp = (int32_t*)(gb + o_lp);
-    double* dv = (double*)(gb + o_v);
+    char* ab = (char*)x.eA.p;
     double* dn = (double*)(ib + o_n);
     double* dr = (double*)(ib + o_r);
-    double* dx = (double*)(ib + o_x);
     int32_t* dk = (int32_t*)(ib + o_k);
     double* dz = (double*)(ib + o_z);
     unsigned* dbad = (unsigned*)(ib + o_bad);
-    double* dA = (double*)x.eA.p;
     double* dM = coupling ? (double*)x.eM.p : nullptr;
     HIPTRY(hipMemcpyAsync(dn, nmult, sizeof(double) * n * nB, hipMemcpyHostToDevice, s));
     HIPTRY(hipMemcpyAsync(dr, rmult, sizeof(double) * n * nB, hipMemcpyHostToDevice, s));
     if (gt_fresh) {
-        ctx->edge_gt_key = std::make_tuple(-1, -1, false);
-        HIPTRY(hipMemcpyAsync(drs, gt.row_start.data(), sizeof(int64_t) * nrs, hipMemcpyHostToDevice, s));
+        HIPTRY(hipMemcpyAsync(gb + o_off, off.data(), sizeof(int64_t) * off.size(), hipMemcpyHostToDevice, s));
+        HIPTRY(hipMemcpyAsync(ab + o_rs, gt.row_start.data(), sizeof(int64_t) * nrs, hipMemcpyHostToDevice, s));
         if (nt) {
-            HIPTRY(hipMemcpyAsync(dlp, gt.term_lp.data(), sizeof(int32_t) * nt, hipMemcpyHostToDevice, s));
-            HIPTRY(hipMemcpyAsync(dv, gt.term_val.data(), sizeof(double) * nt, hipMemcpyHostToDevice, s));
+            HIPTRY(hipMemcpyAsync(ab + o_tl, gt.term_lp.data(), sizeof(int32_t) * nt, hipMemcpyHostToDevice, s));
+            HIPTRY(hipMemcpyAsync(ab + o_tv, gt.term_val.data(), sizeof(double) * nt, hipMemcpyHostToDevice, s));
         }
+        HIPTRY((hipError_t)launch_edge_ell(n, (const int64_t*)(ab + o_rs), (const int32_t*)(ab + o_tl),
+                                           (const double*)(ab + o_tv), (const int64_t*)(gb + o_off),
+                                           (uint16_t*)(gb + o_lp), (double*)(gb + o_v), s));
     }
     if (nout) HIPTRY(hipMemcpyAsync(dk, keep.data(), sizeof(int32_t) * nout, hipMemcpyHostToDevice, s));
     HIPTRY((hipError_t)launch_fill_u32(dbad, 1, 0u, s));
     a.nmult = dn;
     a.rmult = dr;
-    a.row_start = drs;
-    a.term_lp = dlp;
-    a.term_val = dv;
-    a.A = dA;
-    a.rhs = dx;
+    a.ell_off = (const int64_t*)(gb + o_off);
+    a.ell_lp = (const uint16_t*)(gb + o_lp);
+    a.ell_val = (const double*)(gb + o_v);
+    a.A = (double*)(ab + o_A);
+    a.P = (double*)(ab + o_P);
+    a.perm = (int32_t*)(ib + o_perm);
     a.keep = dk;
     a.zeta = dz;
     a.M_out = dM;
     a.nbad = dbad;
     HIPTRY(hipEventRecord(ctx->main.ev[0], s));
-    HIPTRY((hipError_t)launch_edge(a, s));
+    for (int64_t B = 0; B < nB; B += chunk)
+        HIPTRY((hipError_t)launch_edge(a, (int)B, (int)std::min<int64_t>(chunk, nB - B), s));
     HIPTRY(hipEventRecord(ctx->main.ev[1], s));
     unsigned nbad = 0;
     HIPTRY(hipMemcpyAsync(zeta, dz, sizeof(double) * nout * nB, hipMemcpyDeviceToHost, s));

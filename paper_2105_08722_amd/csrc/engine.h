@@ -220,6 +220,7 @@ struct encore_ctx {
     // edge correction: (npcf, lmax, all parities) of the Gaunt table held in
     // main.egt; (-1, ...) when it holds none (guarded by mu)
     std::tuple<int, int, bool> edge_gt_key{-1, -1, false};
+    int64_t edge_ell_len = 0;   // its padded terms
     std::atomic<int> live_grids{0};
 };
 

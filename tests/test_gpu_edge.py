@@ -170,3 +170,28 @@ def test_edge_blocked_solve_many_panels(ctx, strong):
         if strong and b == 0:
             _say("  cond of the first matrix: %.1e" % cond)
         assert np.max(np.abs(z[:, b] - zr)) <= 1e-13 * cond * np.max(np.abs(zr))
+
+
+@pytest.mark.parametrize("N,lmax,nbins,allp", [(3, 10, 3, False), (4, 4, 4, True), (4, 6, 4, False), (4, 7, 4, True),
+                                               (6, 2, 6, False), (5, 4, 5, True), (6, 3, 6, False)])
+def test_edge_solve_sizes(ctx, N, lmax, nbins, allp):
+    """The blocked LU where its steps change: 11 multiplets (one ragged panel), 65 (one
+    column past a panel), 106 and 260 (ragged second panels, a few columns past two
+    outer blocks), 327, 1085 and 2212 (two and three rows per thread of a panel, many
+    outer blocks), with windows far from diagonal, against numpy's LU solve of the
+    device's own coupling matrices, which are symmetric."""
+    n = encore.num_multiplets(N, lmax, allp)
+    nB = encore.num_bin_tuples(N, nbins)
+    _say("edge solve sizes N=%d lmax=%d n=%d nB=%d" % (N, lmax, n, nB))
+    rng = np.random.default_rng(n)
+    R = rng.normal(0.0, 1.0, (n, nB))
+    R[0] = rng.uniform(1.0, 3.0, nB)
+    Nm = rng.normal(0.0, 1.0, (n, nB))
+    z, M, bad = encore.edge_correct(ctx, N, lmax, nbins, Nm, R, allparity=allp, return_coupling=True)
+    assert bad == 0
+    for b in range(min(nB, 3)):
+        assert np.array_equal(M[b], M[b].T)
+        zr = np.linalg.solve(M[b].T, Nm[:, b] / R[0, b])
+        # two backward-stable solvers agree to ~cond(A) * eps
+        cond = np.linalg.cond(M[b])
+        assert np.max(np.abs(z[:, b] - zr)) <= 1e-13 * cond * np.max(np.abs(zr))
