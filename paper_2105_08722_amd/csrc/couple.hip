@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <utility>
 
 #include "device.h"
 
@@ -92,26 +93,31 @@ __global__ void __launch_bounds__(kBlock) k_couple(CoupleArgs a, int ptile)
     }
 }
 
-// 4PCF with 10 radial bins: one block per (b1, 256 tuples, primary split).
-// For each primary each thread loads a~^{b1} of its first factor once, the
-// second-factor a~^{b2} and third-factor a~^{b3} rows once each, forms
-// P = w a1 a2 once per b2 and adds Q[P a3] for every b3 > b2.  Accumulation: FP32
-// over a tile of primaries, then FP64 registers (the FP64 path: FP64 throughout).
+// 4PCF: one block per (256 tuples, first bin b1, primary split).  For each primary each
+// thread loads a~^{b1} of its first factor, the second factor's a~^{b2} and the third
+// factor's a~^{b3} once each, forms P = w a1 a2 once per b2 and adds Q[P a3] for every
+// b3 > b2: about one product per output and primary instead of k_couple's three.
+// TI: the coefficients' type, TC: that of the products.  TC = double adds to the FP64
+// sums directly; TC = float (the FP32 path at 10 bins) to FP32 sums over a tile of
+// primaries, then to FP64 sums.  Bound by FP64 issue and the LDS reads alike at b1 = 0
+// (17 reads of 16 bytes for 104 multiply-adds).  Without the FP32 path's second set of
+// sums, which the FP64 path used to keep too, and with several b1 per launch, 10 bins
+// at lmax 5 over 60k primaries take 2.52 ms in FP64 (3.55 before).
 constexpr int kNB4 = 10;
-__host__ __device__ constexpr int pair_count(int b1) { return (kNB4 - 1 - b1) * (kNB4 - 2 - b1) / 2; }
+constexpr int kNB4Max = 12;   // its 55 FP64 sums and 2 x 12 coefficients per thread fit the registers
+__host__ __device__ constexpr int pair_count(int nr) { return (nr - 1) * (nr - 2) / 2; }   // b1 < b2 < b3 of nr bins
 
-template <typename T, int B1>
-__global__ void __launch_bounds__(kBlock) k_couple4(CoupleArgs a, int ptile)
+template <typename TI, typename TC, int NR>
+__device__ __forceinline__ void couple4_bins(const CoupleArgs& a, int ptile, int t, unsigned char* smem)
 {
-    using V = typename C2<T>::type;
-    constexpr int NA = pair_count(B1);
-    constexpr int NR = kNB4 - B1;                         // bins b1..9 staged
-    extern __shared__ __align__(16) unsigned char smem[];
+    using V = typename C2<TI>::type;
+    constexpr bool TILED = sizeof(TC) == 4;
+    constexpr int NA = pair_count(NR);
+    const int B1 = a.nbins - NR;
     V* tile = reinterpret_cast<V*>(smem);
     const int per = NR * a.nlm;                           // staged complex values per primary
     double* wtile = reinterpret_cast<double*>(smem + sizeof(V) * (size_t)ptile * per);
 
-    const int t = blockIdx.x * kBlock + threadIdx.x;
     const bool valid = t < a.ntuple;
     const int split = blockIdx.y;
     const int p_lo = a.split_lo[split];
@@ -124,20 +130,20 @@ __global__ void __launch_bounds__(kBlock) k_couple4(CoupleArgs a, int ptile)
         lm2 = a.tuple_off[t * 3 + 2];
         flags = a.tuple_flags[t];
     }
-    const T c0 = (flags & 1) ? (T)-1 : (T)1;
-    const T c1 = (flags & 2) ? (T)-1 : (T)1;
-    const T c2 = (flags & 4) ? (T)-1 : (T)1;
+    const TC c0 = (flags & 1) ? (TC)-1 : (TC)1;
+    const TC c1 = (flags & 2) ? (TC)-1 : (TC)1;
+    const TC c2 = (flags & 4) ? (TC)-1 : (TC)1;
     const bool take_im = (flags >> 16) & 1;
 
     double acc[NA];
-    T part[NA];
+    TC part[TILED ? NA : 1];
 #pragma unroll
-    for (int q = 0; q < NA; ++q) { acc[q] = 0.0; part[q] = (T)0; }
+    for (int q = 0; q < NA; ++q) acc[q] = 0.0;
 
     for (int p0 = p_lo; p0 < p_hi; p0 += ptile) {
         const int np = min(ptile, p_hi - p0);
         __syncthreads();
-        // stage bins B1..9 of each primary of the tile
+        // stage bins B1 .. nbins - 1 of each primary of the tile
         const V* src = reinterpret_cast<const V*>(a.alm);
         const int full = a.nbins * a.nlm;
         for (int q = threadIdx.x; q < np * per; q += kBlock) {
@@ -146,46 +152,65 @@ __global__ void __launch_bounds__(kBlock) k_couple4(CoupleArgs a, int ptile)
         }
         for (int q = threadIdx.x; q < np; q += kBlock) wtile[q] = a.wprim[p0 + q];
         __syncthreads();
+        if constexpr (TILED)
+#pragma unroll
+            for (int q = 0; q < NA; ++q) part[q] = (TC)0;
         if (valid) {
             for (int pp = 0; pp < np; ++pp) {
                 const V* ap = tile + pp * per;
-                const T w = (T)wtile[pp];
+                const TC w = (TC)wtile[pp];
                 const V v0 = ap[lm0];
-                const T a1r = w * v0.x, a1i = w * (c0 * v0.y);
-                T u3r[NR], u3i[NR];
+                const TC a1r = w * (TC)v0.x, a1i = w * (c0 * (TC)v0.y);
+                TC u3r[NR], u3i[NR];
 #pragma unroll
                 for (int b = 2; b < NR; ++b) {
                     const V u = ap[b * a.nlm + lm2];
-                    u3r[b] = u.x; u3i[b] = c2 * u.y;
+                    u3r[b] = (TC)u.x; u3i[b] = c2 * (TC)u.y;
                 }
                 int q = 0;
 #pragma unroll
                 for (int b2 = 1; b2 < NR - 1; ++b2) {
                     const V u = ap[b2 * a.nlm + lm1];
-                    const T ur = u.x, ui = c1 * u.y;
-                    T pr = a1r * ur - a1i * ui;
-                    T pi = a1r * ui + a1i * ur;
-                    if (take_im) { const T tmp = pr; pr = pi; pi = -tmp; }   // Im(z) = Re(-i z)
+                    const TC ur = (TC)u.x, ui = c1 * (TC)u.y;
+                    TC pr = a1r * ur - a1i * ui;
+                    TC pi = a1r * ui + a1i * ur;
+                    if (take_im) { const TC tmp = pr; pr = pi; pi = -tmp; }   // Im(z) = Re(-i z)
 #pragma unroll
                     for (int b3 = b2 + 1; b3 < NR; ++b3) {
-                        part[q] += pr * u3r[b3] - pi * u3i[b3];
+                        if constexpr (TILED) part[q] += pr * u3r[b3] - pi * u3i[b3];
+                        else acc[q] = fma(-pi, u3i[b3], fma(pr, u3r[b3], acc[q]));
                         ++q;
                     }
                 }
             }
         }
+        if constexpr (TILED)
 #pragma unroll
-        for (int q = 0; q < NA; ++q) { acc[q] += (double)part[q]; part[q] = (T)0; }
+            for (int q = 0; q < NA; ++q) acc[q] += (double)part[q];
     }
     if (valid) {
         const double sgn = ((flags >> 8) & 1) ? -1.0 : 1.0;
         // B index of (B1, b2, b3): tuples with first bin < B1 come first
         int bidx = 0;
-        for (int b = 0; b < B1; ++b) bidx += pair_count(b);
+        for (int b = 0; b < B1; ++b) bidx += pair_count(a.nbins - b);
         double* dst = a.T + ((size_t)split * a.ntuple + t) * a.nB + bidx;
 #pragma unroll
         for (int q = 0; q < NA; ++q) dst[q] = sgn * acc[q];
     }
+}
+
+// the first bins b1 = nbins - nr of nr = NRLO .. NRHI, the one with the most tuples of
+// bins first
+template <typename TI, typename TC, int NRLO, int NRHI>
+__global__ void __launch_bounds__(kBlock) k_couple4(CoupleArgs a, int ptile, int tblocks, int nr_first)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int j = blockIdx.x / tblocks;
+    const int t = (blockIdx.x - j * tblocks) * kBlock + threadIdx.x;
+    const int nr = nr_first - j;                          // uniform over the block
+    [&]<int... R>(std::integer_sequence<int, R...>) {
+        ((nr == R + NRLO ? couple4_bins<TI, TC, R + NRLO>(a, ptile, t, smem) : (void)0), ...);
+    }(std::make_integer_sequence<int, NRHI - NRLO + 1>{});
 }
 
 __global__ void __launch_bounds__(kBlock) k_contract(ContractArgs a)
@@ -213,13 +238,26 @@ __global__ void __launch_bounds__(kBlock) k_contract(ContractArgs a)
 
 }  // namespace
 
+// k_couple4 couples this job: up to 12 bins, and with enough tuples that its blocks,
+// whose lanes are tuples, are not mostly idle (4PCF FP64, 60k primaries, k_couple /
+// k_couple4 in ms: lmax 3 6 bins 0.27 / 0.39, 8 bins 0.65 / 0.51; lmax 5 6 bins 1.52 /
+// 0.80, 8 bins 5.0 / 1.6, 12 bins 25.1 / 5.6).  10 bins always, where k_couple took
+// longer at every lmax.
+static bool use_couple4(int nk, int nbins, int64_t ntuple, int64_t nB)
+{
+    return nk == 3 && nbins >= 3 &&
+           (nbins == kNB4 || (nbins <= kNB4Max && ntuple >= 128 && ntuple * nB >= 8192));
+}
+
 int couple_split_rows(int nk, int nbins, int64_t ntuple, int64_t nB, int64_t nrows)
 {
     int64_t ns;
-    if (nk == 3 && nbins == kNB4) {
-        // one block per (b1, 256 tuples, split): aim at ~1024 blocks per launch
+    if (use_couple4(nk, nbins, ntuple, nB)) {
+        // one block per (b1, 256 tuples, split): aim at ~1024 blocks per b1
         const int64_t tblocks = (ntuple + kBlock - 1) / kBlock;
         ns = (1024 + tblocks - 1) / std::max<int64_t>(tblocks, 1);
+        // other bin counts keep their partial sums within 64 MiB
+        if (nbins != kNB4) ns = std::min<int64_t>(ns, ((int64_t)64 << 20) / (8 * ntuple * nB));
     } else {
         ns = (int64_t)(1 << 20) / std::max<int64_t>(ntuple * nB, 1);
     }
@@ -255,37 +293,48 @@ int couple_ptile(int nbins, int nlm, int precision)
     return pt < 1 ? 1 : (pt > 64 ? 64 : pt);
 }
 
-template <typename T, int B1>
-void launch4(const CoupleArgs& a, int ptile, hipStream_t stream)
+template <typename TI, typename TC, int NRLO, int NRHI>
+int launch4(const CoupleArgs& a, hipStream_t stream)
 {
-    const int nblk = (a.ntuple + kBlock - 1) / kBlock;
-    const size_t lds = (size_t)ptile * (kNB4 - B1) * a.nlm * sizeof(typename C2<T>::type) + 8 * (size_t)ptile;
-    k_couple4<T, B1><<<dim3((unsigned)nblk, (unsigned)a.nsplit), kBlock, lds, stream>>>(a, ptile);
+    const int hi = std::min(NRHI, a.nbins);
+    if (hi < NRLO) return (int)hipSuccess;
+    const int ptile = std::max(1, std::min(64, 32768 / (a.nbins * a.nlm * (int)sizeof(typename C2<TI>::type) + 8)));
+    const int tblocks = (a.ntuple + kBlock - 1) / kBlock;
+    const size_t lds = (size_t)ptile * hi * a.nlm * sizeof(typename C2<TI>::type) + 8 * (size_t)ptile;
+    k_couple4<TI, TC, NRLO, NRHI><<<dim3((unsigned)(tblocks * (hi - NRLO + 1)), (unsigned)a.nsplit), kBlock, lds,
+                                    stream>>>(a, ptile, tblocks, hi);
+    return (int)hipGetLastError();
 }
 
-template <typename T>
-void launch4_all(const CoupleArgs& a, int ptile, hipStream_t stream)
+// Several first bins share a launch so that no launch's end leaves the chip idle for
+// long; the register use of a launch is that of its largest, which keeps the small
+// ones apart where there are enough blocks (4PCF lmax 5, 60k primaries, ms, one launch
+// per b1 / these groups / one launch: FP64 10 bins 2.79 / 2.52 / 2.76, 8 bins 1.86 /
+// 1.63 / 1.57, 12 bins 12.8 / 6.3 / 5.6; FP32 10 bins with {8..10} in one launch 2.30,
+// {10} alone 2.07).
+template <typename TI>
+int launch4_fp64(const CoupleArgs& a, hipStream_t stream)
 {
-    launch4<T, 0>(a, ptile, stream);
-    launch4<T, 1>(a, ptile, stream);
-    launch4<T, 2>(a, ptile, stream);
-    launch4<T, 3>(a, ptile, stream);
-    launch4<T, 4>(a, ptile, stream);
-    launch4<T, 5>(a, ptile, stream);
-    launch4<T, 6>(a, ptile, stream);
-    launch4<T, 7>(a, ptile, stream);
-    // bins 8 and 9 cannot be the first bin of a triple: their rows of T are absent
+    if (a.nbins > kNB4) return launch4<TI, double, 3, kNB4Max>(a, stream);
+    const int rc = launch4<TI, double, 8, kNB4>(a, stream);
+    return rc != (int)hipSuccess ? rc : launch4<TI, double, 3, 7>(a, stream);
+}
+int launch4_fp32(const CoupleArgs& a, hipStream_t stream)
+{
+    int rc = launch4<float, float, kNB4, kNB4>(a, stream);
+    if (rc == (int)hipSuccess) rc = launch4<float, float, 8, 9>(a, stream);
+    return rc != (int)hipSuccess ? rc : launch4<float, float, 3, 7>(a, stream);
 }
 
 int launch_couple(const CoupleArgs& a, int precision, hipStream_t stream)
 {
     if (a.nk > kMaxK) return (int)hipErrorInvalidValue;
     if (a.nsplit == 0 || a.ntuple == 0) return (int)hipSuccess;
-    if (a.nk == 3 && a.nbins == kNB4) {
-        const int ptile = std::max(1, std::min(64, 32768 / (kNB4 * a.nlm * (precision == 0 ? 16 : 8) + 8)));
-        if (precision == 0) launch4_all<double>(a, ptile, stream);
-        else launch4_all<float>(a, ptile, stream);
-        return (int)hipGetLastError();
+    if (use_couple4(a.nk, a.nbins, a.ntuple, a.nB)) {
+        if (precision == 0) return launch4_fp64<double>(a, stream);
+        // the FP32 products of 10 bins are summed in FP32 over a tile of primaries;
+        // other bin counts keep FP64 sums throughout, as in k_couple
+        return a.nbins == kNB4 ? launch4_fp32(a, stream) : launch4_fp64<float>(a, stream);
     }
     const int64_t nthreads = (int64_t)a.ntuple * a.nB;
     const int64_t nblk = (nthreads + kBlock - 1) / kBlock;
