@@ -151,10 +151,10 @@ int encore_npcf(encore_ctx* ctx, const encore_grid* grid, int npcf, int lmax, in
 
 /*
  * The same multiplets for several catalogs at once (one job per grid).  All jobs
- * share npcf, lmax, the bins and the flags.  The gather runs as ONE persistent launch per slice of primaries: waves
- * pull (catalog, primary, bin group) work items from device work queues, so
- * catalogs of uneven size and neighbour count share the GPU without per-job
- * launches.  The coupling and FP64 sums stay per job.
+ * share npcf, lmax, the bins and the flags.  The gather runs as ONE launch per slice of primaries over the
+ * (catalog, primary, bin group) work items of all jobs -- many items: persistent
+ * waves that pull them from device work queues -- so catalogs of uneven size and
+ * neighbour count share the GPU without per-job launches.  The coupling and FP64 sums stay per job.
  *  grids   [njobs] grids built on ctx (may repeat).
  *  zeta    host FP64 [njobs][n_multiplets * n_bin_tuples].
  *  zeta_len length of zeta in elements (>= njobs * n_multiplets * n_bin_tuples).
@@ -183,7 +183,7 @@ int encore_npcf_batch(encore_ctx* ctx, const encore_grid* const* grids, int njob
  *  - Continuous batching: each lane iteration runs one slice of at most
  *    slice_rows primaries taken, oldest job first, from every admitted idle job
  *    of the same class (same npcf, lmax, bins, precision and parity) in one
- *    persistent gather launch; jobs that arrive meanwhile join at the next
+ *    gather launch; jobs that arrive meanwhile join at the next
  *    iteration.  Lanes run concurrently, so their work overlaps on the device.
  *  - A job's rows are reduced in a fixed order that depends only on the job, so
  *    its result is bit-identical to encore_npcf on the same catalog whatever it

@@ -54,6 +54,16 @@ int fill_primaries(Exec& x, const encore_grid* grid, const int64_t* subset, int6
 
 namespace {
 
+// The accepted pairs that the gathers counted at d (synchronous).
+hipError_t count_pairs(const unsigned long long* d, unsigned long long* total)
+{
+    unsigned long long h[kPairCounters * kPairStride];
+    const hipError_t e = hipMemcpy(h, d, kPairBytes, hipMemcpyDeviceToHost);
+    *total = 0;
+    for (int i = 0; e == hipSuccess && i < kPairCounters; ++i) *total += h[i * kPairStride];
+    return e;
+}
+
 // Primary list of one job into x.prim; returns count in *np.
 int make_primaries(Exec& x, const encore_grid* grid, const int64_t* subset, int64_t k, int64_t* np)
 {
@@ -145,10 +155,10 @@ int run_jobs(encore_ctx* ctx, Exec& x, const DevTables* tb, int64_t cap, const s
     const int64_t outs = acc_len(pl, tb);
     if ((rc = ensure(x.Tjob, sizeof(double) * (size_t)(njobs * outs)))) return rc;
     if ((rc = ensure(x.zeta, sizeof(double) * (size_t)njobs * std::max<size_t>(need, 1)))) return rc;
-    if ((rc = ensure(x.misc, 64))) return rc;
+    if ((rc = ensure(x.misc, kPairBytes))) return rc;
     unsigned long long* d_pairs = (unsigned long long*)x.misc.p;
     HIPTRY((hipError_t)launch_fill((double*)x.Tjob.p, njobs * outs, 0.0, s));
-    HIPTRY((hipError_t)launch_fill((double*)d_pairs, 1, 0.0, s));   // zero bits = 0ull
+    HIPTRY((hipError_t)launch_fill((double*)d_pairs, kPairBytes / 8, 0.0, s));   // zero bits = 0ull
 
     std::vector<int64_t> srows(jobs.size());
     for (size_t j = 0; j < jobs.size(); ++j) srows[j] = job_split_rows(pl, tb, jobs[j].nprim, cap);
@@ -209,7 +219,7 @@ int run_jobs(encore_ctx* ctx, Exec& x, const DevTables* tb, int64_t cap, const s
     HIPTRY(hipEventElapsedTime(&ms_c, x.ev[1], x.ev[2]));
     HIPTRY(hipEventElapsedTime(&ms_tot, x.ev[0], x.ev[3]));
     unsigned long long pairs = 0;
-    HIPTRY(hipMemcpy(&pairs, d_pairs, sizeof(pairs), hipMemcpyDeviceToHost));
+    HIPTRY(count_pairs(d_pairs, &pairs));
     ctx->timings[0] = ms_tot;
     ctx->timings[1] = t_gather;
     ctx->timings[2] = t_couple;
@@ -491,7 +501,7 @@ int encore_npcf_splits(encore_ctx* ctx, const encore_grid* data_grid, const enco
         const hipStream_t s = x.s;
         int rc2;
         // every part's data are the data grid's
-        if ((rc2 = ensure(x.misc, 64))) return rc2;
+        if ((rc2 = ensure(x.misc, kPairBytes))) return rc2;
         int* d_bad = (int*)((char*)x.misc.p + 16);
         HIPTRY((hipError_t)launch_fill_u32((unsigned*)d_bad, 1, 0u, s));
         for (int k = 0; k < nsplit; ++k) HIPTRY((hipError_t)launch_split_check(split_grids[k]->g, gD, d_bad, s));
@@ -583,7 +593,7 @@ int encore_npcf_splits(encore_ctx* ctx, const encore_grid* data_grid, const enco
         if ((rc2 = ensure(x.cache, rb * (size_t)gD.n))) return rc2;
         const int64_t cap = cap_rows(pl);
         unsigned long long* d_pairs = (unsigned long long*)x.misc.p;
-        HIPTRY((hipError_t)launch_fill((double*)d_pairs, 1, 0.0, s));
+        HIPTRY((hipError_t)launch_fill((double*)d_pairs, kPairBytes / 8, 0.0, s));
         HIPTRY(hipEventRecord(x.ev[1], s));
         for (int64_t r0 = 0; r0 < gD.n; r0 += cap) {
             const int64_t r1 = std::min<int64_t>(gD.n, r0 + cap);
@@ -599,7 +609,7 @@ int encore_npcf_splits(encore_ctx* ctx, const encore_grid* data_grid, const enco
         float ms_cache = 0.f;
         HIPTRY(hipEventElapsedTime(&ms_cache, x.ev[1], x.ev[2]));
         unsigned long long pairs_cache = 0;
-        HIPTRY(hipMemcpy(&pairs_cache, d_pairs, sizeof(pairs_cache), hipMemcpyDeviceToHost));
+        HIPTRY(count_pairs(d_pairs, &pairs_cache));
 
         // per part two jobs: the data primaries against the part's randoms (plus
         // their cached rows), and the part's random primaries against data + randoms
@@ -868,7 +878,7 @@ int encore_debug_alm(encore_ctx* ctx, const encore_grid* grid, int lmax, int nbi
     NpcfPlan gpl;
     gpl.lmax = lmax; gpl.prec = cprec; gpl.nbins = nbins;
     const int nbg = ctx_nbg(ctx, gpl);   // the configuration encore_npcf launches
-    if (e == hipSuccess) e = (hipError_t)launch_gather(ga, lmax, prec, nbg, false, s);
+    if (e == hipSuccess) e = (hipError_t)launch_gather(ga, lmax, prec, nbg, 0, s);
     if (e == hipSuccess)
         e = (hipError_t)launch_to_double(x.alm.p, prec == 0 ? 0 : 1, nlaunch * per, (double*)x.zeta.p, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -102,6 +102,14 @@ inline void finish_seg(GatherSeg& s)
     const double margin = 1e-6 * nmax > 1e-3 ? 1e-6 * nmax : 1e-3;
     s.frame_eps = margin * cmin;
 }
+// Counters that every work item increments lie in cache lines of their own, and the
+// accepted pairs are counted in many of them: atomics on one line are done one after
+// the other, about 12.5 ns each, and with one counter of the pairs they set the time of
+// a gather (4 million items of the 800k-point 4PCF: 50 ms).
+constexpr int kPairCounters = 128, kPairStride = 16;   // 64-bit words
+constexpr int kQueueStride = 32;                       // 32-bit words
+constexpr size_t kPairBytes = sizeof(unsigned long long) * kPairCounters * kPairStride;
+constexpr size_t kQueueBytes = sizeof(unsigned) * 8 * kQueueStride;
 struct GatherArgs {
     const GatherSeg* segs;   // device array
     int nseg;
@@ -114,14 +122,19 @@ struct GatherArgs {
     void* alm;               // output rows
     double* wprim;           // output: weight of each row's primary
     const double* kappa;     // [nlm] final scale of the monic recurrence
-    unsigned long long* npairs;  // optional: += accepted pairs (null: not counted)
+    // optional (null: not counted): kPairCounters counters, kPairStride apart, that
+    // together are incremented by the accepted pairs
+    unsigned long long* npairs;
     // persistent mode (queues != null): waves pull items from 8 queues (one per
     // XCD, contiguous item ranges) and steal from the others when theirs is empty
-    unsigned* queues;        // [8] counters, zero at launch
+    unsigned* queues;        // 8 counters, kQueueStride apart, zero at launch
+    int xcd_run;             // static grid: consecutive workgroups per XCD (set by launch_gather)
 };
 // precision: 0 = FP64, 1 = FP32.  nbg: bins per work item (0 or a value without
-// a compiled variant: the default).  persistent: grid sized to the resident waves.
-int launch_gather(const GatherArgs& a, int lmax, int precision, int nbg, bool persistent, hipStream_t stream);
+// a compiled variant: the default).  grid: 0 one wave per work item, 1 persistent (a
+// grid of the resident waves, where compiled and a.queues is given), -1 by the number
+// of work items.
+int launch_gather(const GatherArgs& a, int lmax, int precision, int nbg, int grid, hipStream_t stream);
 // alm row row0 + r += cache row prim[r], r < nrows (rows of row_cplx complex
 // values; precision 0: FP64, else FP32)
 int launch_add_cached(void* alm, int precision, int row0, int nrows, const int32_t* prim, const void* cache,

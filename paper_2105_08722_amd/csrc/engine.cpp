@@ -470,8 +470,8 @@ int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl
     if ((rc = ensure(segs, sizeof(GatherSeg) * hsegs.size()))) return rc;
     if ((rc = ensure(splits, sizeof(int32_t) * (size_t)(2 * nsplit + 2 * nred)))) return rc;
     if ((rc = ensure(redp, sizeof(double*) * (size_t)nred))) return rc;
-    if ((rc = ensure(x.queues, 64))) return rc;
-    if ((rc = ensure(x.misc, 64))) return rc;
+    if ((rc = ensure(x.queues, kQueueBytes))) return rc;
+    if ((rc = ensure(x.misc, kPairBytes))) return rc;
     std::vector<int32_t> hsplit;
     hsplit.insert(hsplit.end(), slo.begin(), slo.end());
     hsplit.insert(hsplit.end(), shi.begin(), shi.end());
@@ -481,10 +481,8 @@ int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl
     HIPTRY(hipMemcpyAsync(splits.p, hsplit.data(), sizeof(int32_t) * hsplit.size(), hipMemcpyHostToDevice, s));
     HIPTRY(hipMemcpyAsync(redp.p, rdst.data(), sizeof(double*) * rdst.size(), hipMemcpyHostToDevice, s));
     const int32_t* dsp = (const int32_t*)splits.p;
-    // several catalogs: the persistent grid (work stealing across XCD queues) unless
-    // ENCORE_GATHER_PERSISTENT says otherwise (0: static grid, 1: always persistent)
-    L.persistent = hsegs.size() > 1;
-    if (const char* e = getenv("ENCORE_GATHER_PERSISTENT")) L.persistent = atoi(e) != 0;
+    // ENCORE_GATHER_PERSISTENT forces the gather's grid (0: static, 1: persistent)
+    if (const char* e = getenv("ENCORE_GATHER_PERSISTENT")) L.grid = atoi(e) != 0;
 
     GatherArgs& ga = L.ga;
     memset(&ga, 0, sizeof(ga));
@@ -546,7 +544,7 @@ int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl
 int launch_slice_gather(const SliceLaunch& L, const NpcfPlan& pl, hipStream_t s)
 {
     if (L.rows == 0) return ENCORE_OK;
-    HIPTRY((hipError_t)launch_gather(L.ga, pl.lmax, gather_precision(pl.prec), pl.nbg, L.persistent, s));
+    HIPTRY((hipError_t)launch_gather(L.ga, pl.lmax, gather_precision(pl.prec), pl.nbg, L.grid, s));
     const int row_cplx = pl.nbins * (pl.lmax + 1) * (pl.lmax + 2) / 2;
     for (const CacheAdd& c : L.adds)
         HIPTRY((hipError_t)launch_add_cached(L.ga.alm, pl.prec == 0 ? 0 : 1, c.row0, c.nrows, c.prim, c.cache,

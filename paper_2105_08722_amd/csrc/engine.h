@@ -168,7 +168,7 @@ struct CacheAdd {
 };
 struct SliceLaunch {
     int64_t rows = 0;
-    bool persistent = false;
+    int grid = -1;                // of the gather (launch_gather)
     std::vector<CacheAdd> adds;   // after the gather
     GatherArgs ga;
     CoupleArgs ca;

@@ -47,10 +47,12 @@ constexpr int kCap = 128;          // stack capacity per bin (pairs): at most 63
 constexpr int kRowsPerBatch = 64;  // rows set up per lane-parallel pass
 constexpr int kSegPerRow = 6;      // <= 2 x-ranges x 3 periodic images
 constexpr int kSegCap = kRowsPerBatch * kSegPerRow;
-// Waves of a block are independent (no block barriers); they take the same bin
-// group of kWavesPerBlock consecutive rows, so nearly the same candidate stream
-// runs on one compute unit and its vector L1 serves the repeats.
-constexpr int kWavesPerBlock = 4;
+// One wave per workgroup: its registers and LDS are free for the next item as soon as
+// it ends.  Four waves of consecutive rows per workgroup, which shared one compute
+// unit's vector L1, waited for their slowest (5PCF-like primaries, a random 20,000 of a
+// 200k-point wedge, lmax 5, ms, 4 waves / 1 wave: FP32 2.88 / 2.44, FP64 5.54 / 4.68;
+// every primary of a 100k-point box 6.77 / 6.84 and 13.07 / 12.34).
+constexpr int kWavesPerBlock = 1;
 constexpr int kRedCh = 16;         // accumulator values per pass of the lane reduction
 
 __host__ __device__ constexpr int nlm_of(int L) { return (L + 1) * (L + 2) / 2; }
@@ -508,10 +510,10 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
 
     // Item j -> quad j / kWavesPerBlock = (row block, bin group), row = block *
     // kWavesPerBlock + j % kWavesPerBlock.  Rows are cell-sorted primaries, so the
-    // waves of one quad scan almost the same cells.  A static grid gives each XCD
-    // (block b runs on XCD b % 8) a contiguous run of quads, so neighbouring
+    // waves of one quad scan almost the same cells.  A static grid gives the XCDs
+    // (block b runs on XCD b % 8) contiguous runs of quads in turn, so neighbouring
     // primaries share that XCD's L2; the persistent grid pulls items from 8
-    // contiguous queues the same way.
+    // contiguous queues.
     const int64_t nquads = ((int64_t)a.nrows + kWavesPerBlock - 1) / kWavesPerBlock * a.ngroups;
     const int64_t nitems = nquads * kWavesPerBlock;
     const int home = blockIdx.x & 7;
@@ -520,7 +522,7 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
             const int qi = (home + t) & 7;
             const int64_t lo = nitems * qi / 8, hi = nitems * (qi + 1) / 8;
             unsigned got = 0;
-            if (lane == 0) got = atomicAdd(&a.queues[qi], 1u);
+            if (lane == 0) got = atomicAdd(&a.queues[qi * kQueueStride], 1u);
             got = __builtin_amdgcn_readfirstlane(got);
             if (lo + (int64_t)got < hi) return lo + (int64_t)got;
         }
@@ -772,7 +774,7 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
         unsigned long long tot = pairs;
 #pragma unroll
         for (int k = 0; k < NBG; ++k) tot += (unsigned long long)(top[k] - k * kCap);
-        atomicAdd(a.npairs, tot);
+        atomicAdd(&a.npairs[(blockIdx.x & (kPairCounters - 1)) * kPairStride], tot);
     }
 
     // ---- flush partial stacks (missing lanes add zero-weight pairs)
@@ -900,8 +902,9 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
     if constexpr (PERS) {
         for (int64_t item = pop(); item >= 0 && item < nitems; item = pop()) work(item);
     } else {
-        const int nblk = gridDim.x;
-        const int bid = (blockIdx.x % 8) * (nblk / 8) + blockIdx.x / 8;
+        // a.xcd_run consecutive workgroups' worth of items per XCD in turn
+        const unsigned slot = blockIdx.x / 8, run = (unsigned)a.xcd_run;
+        const unsigned bid = (slot / run * 8 + blockIdx.x % 8) * run + slot % run;
         const int64_t item = (int64_t)bid * kWavesPerBlock + wib;
         if (item < nitems) work(item);
     }
@@ -914,19 +917,26 @@ struct KernelCfg {
     int nm;                 // number of m groups
     int m0[2], m1[2];
     const void* fn[2];      // static grid
-    const void* fnp[2];     // persistent grid
+    const void* fnp[2];     // persistent grid (null: the static grid is faster at every size)
     int lds;                // bytes per block
 };
 
 template <typename T, int L, int NBG, int M0, int M1, bool PERS, bool COMP>
 const void* kfn() { return reinterpret_cast<const void*>(&k_gather<T, L, NBG, M0, M1, PERS, COMP>); }
 
-template <typename T, int L, int NBG, bool COMP = false>
+// PERSOK: also as a persistent kernel.  Its item loop holds about 15 more registers:
+// where that costs a resident wave (FP64 and FP32-path accumulators at lmax 4 and 6),
+// and in FP64 from lmax 4 on, where the item's own arithmetic dominates, the static grid
+// is as fast or faster (ms, static / persistent, over 100k points: lmax 4 FP64 9.4 /
+// 11.5, FP32 path 7.8 / 9.6; lmax 5 FP64 12.3 / 12.9; the dense random splits of 16
+// catalogs in FP64 24.3 / 24.9).
+template <typename T, int L, int NBG, bool COMP = false, bool PERSOK = true>
 KernelCfg cfg1()
 {
     KernelCfg c{};
     c.nbg = NBG; c.nm = 1; c.m0[0] = 0; c.m1[0] = L;
-    c.fn[0] = kfn<T, L, NBG, 0, L, false, COMP>(); c.fnp[0] = kfn<T, L, NBG, 0, L, true, COMP>();
+    c.fn[0] = kfn<T, L, NBG, 0, L, false, COMP>();
+    if constexpr (PERSOK) c.fnp[0] = kfn<T, L, NBG, 0, L, true, COMP>();
     c.lds = kWavesPerBlock * wave_lds_bytes<T, NBG, COMP>();
     return c;
 }
@@ -936,9 +946,9 @@ KernelCfg cfg2()
     KernelCfg c{};
     c.nbg = NBG; c.nm = 2;
     c.m0[0] = 0; c.m1[0] = MS - 1;
-    c.fn[0] = kfn<T, L, NBG, 0, MS - 1, false, COMP>(); c.fnp[0] = kfn<T, L, NBG, 0, MS - 1, true, COMP>();
+    c.fn[0] = kfn<T, L, NBG, 0, MS - 1, false, COMP>();
     c.m0[1] = MS; c.m1[1] = L;
-    c.fn[1] = kfn<T, L, NBG, MS, L, false, COMP>(); c.fnp[1] = kfn<T, L, NBG, MS, L, true, COMP>();
+    c.fn[1] = kfn<T, L, NBG, MS, L, false, COMP>();
     c.lds = kWavesPerBlock * wave_lds_bytes<T, NBG, COMP>();
     return c;
 }
@@ -974,9 +984,9 @@ KernelCfg config(int lmax, int precision, int nbg)
         case 1: return nbg == 4 ? cfg1<float, 1, 4, true>() : cfg1<float, 1, 2, true>();
         case 2: return cfg1<float, 2, 2, true>();
         case 3: return cfg1<float, 3, 2, true>();
-        case 4: return cfg1<float, 4, 2, true>();
+        case 4: return cfg1<float, 4, 2, true, false>();
         case 5: return nbg == 1 ? cfg1<float, 5, 1, true>() : cfg1<float, 5, 2, true>();
-        case 6: return cfg1<float, 6, 1, true>();
+        case 6: return cfg1<float, 6, 1, true, false>();
         case 7: return cfg1<float, 7, 1, true>();
         case 8: return cfg1<float, 8, 1, true>();
         case 9: return cfg2<float, 9, 1, 5, true>();
@@ -1002,11 +1012,11 @@ KernelCfg config(int lmax, int precision, int nbg)
         case 1: return cfg1<double, 1, 2>();
         case 2: return cfg1<double, 2, 2>();
         case 3: return cfg1<double, 3, 2>();
-        case 4: return cfg1<double, 4, 2>();
-        case 5: return cfg1<double, 5, 2>();
-        case 6: return cfg1<double, 6, 1>();
-        case 7: return cfg1<double, 7, 1>();
-        case 8: return cfg1<double, 8, 1>();
+        case 4: return cfg1<double, 4, 2, false, false>();
+        case 5: return cfg1<double, 5, 2, false, false>();
+        case 6: return cfg1<double, 6, 1, false, false>();
+        case 7: return cfg1<double, 7, 1, false, false>();
+        case 8: return cfg1<double, 8, 1, false, false>();
         case 9: return cfg2<double, 9, 1, 5>();
         case 10: return cfg2<double, 10, 1, 4>();
         }
@@ -1046,38 +1056,68 @@ void gather_tables(int lmax, double* kappa)
     }
 }
 
-int launch_gather(const GatherArgs& a0, int lmax, int precision, int nbg, bool persistent, hipStream_t stream)
+// From this many work items on a launch takes the persistent grid: resident waves pull
+// items instead of a workgroup starting for each, 3 to 10% faster with many items per
+// wave (lmax 5 FP32 over 100k points, 500k items: 6.84 -> 6.40 ms); below, the waves'
+// last, vain pulls from the queues cost more than that saves (6,000 items: 42 -> 78 us;
+// 50,000: 365 -> 381 us).
+constexpr int64_t kPersistentItems = 1 << 18;
+
+namespace {
+
+// Resident workgroups of a persistent kernel on the current device.
+int resident_blocks(const void* fn, int lds, int64_t* blocks)
+{
+    struct Known { const void* fn; int dev; int64_t blocks; };
+    static thread_local std::vector<Known> known;
+    int dev = 0, per_cu = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return (int)e;
+    for (const Known& k : known)
+        if (k.fn == fn && k.dev == dev) {
+            *blocks = k.blocks;
+            return (int)hipSuccess;
+        }
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave * kWavesPerBlock, (size_t)lds);
+    if (e != hipSuccess) return (int)e;
+    *blocks = (int64_t)std::max(1, per_cu) * cus;
+    known.push_back(Known{fn, dev, *blocks});
+    return (int)hipSuccess;
+}
+
+}  // namespace
+
+int launch_gather(const GatherArgs& a0, int lmax, int precision, int nbg, int grid, hipStream_t stream)
 {
     const KernelCfg c = config(lmax, precision, nbg);
     if (!c.fn[0]) return (int)hipErrorInvalidValue;
     GatherArgs a = a0;
     a.group_bins = c.nbg;
     a.ngroups = (a.nbins + c.nbg - 1) / c.nbg;
-    if (!persistent) a.queues = nullptr;
-    if (persistent && !a.queues) return (int)hipErrorInvalidValue;
     const int64_t quads = ((int64_t)a.nrows + kWavesPerBlock - 1) / kWavesPerBlock * a.ngroups;
     if (quads == 0) return (int)hipSuccess;
+    const bool persistent = c.fnp[0] && a.queues &&
+                            (grid == 1 || (grid < 0 && quads * kWavesPerBlock >= kPersistentItems));
+    if (!persistent) a.queues = nullptr;
     for (int g = 0; g < c.nm; ++g) {
         const void* fn = persistent ? c.fnp[g] : c.fn[g];
-        int64_t blocks;
+        int64_t blocks = quads;
         if (persistent) {
-            // one block per resident block slot
-            int dev = 0, per_cu = 0;
-            hipDeviceProp_t prop;
-            hipError_t e = hipGetDevice(&dev);
-            if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
-            if (e == hipSuccess)
-                e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave * kWavesPerBlock,
-                                                                 (size_t)c.lds);
-            if (e != hipSuccess) return (int)e;
-            blocks = std::max(1, per_cu) * (int64_t)prop.multiProcessorCount;
-            blocks = std::min<int64_t>(blocks, quads);
-            const int rc = launch_fill_u32(a.queues, 8, 0u, stream);
+            int64_t resident = 0;
+            int rc = resident_blocks(fn, c.lds, &resident);
+            if (rc == 0) rc = launch_fill_u32(a.queues, 8 * kQueueStride, 0u, stream);
             if (rc != 0) return rc;
-        } else {
-            blocks = quads;
+            blocks = std::min<int64_t>(resident, quads);
         }
-        blocks = (blocks + 7) / 8 * 8;
+        // runs of at most 1024 items per XCD, 16 runs each or more: with one contiguous
+        // eighth of the items per XCD those of sparse regions were idle at the end
+        // (dense random splits, FP64: 27.5 -> 24.3 ms)
+        int64_t run = 1;
+        while (run < 1024 && 256 * run <= blocks) run *= 2;
+        a.xcd_run = (int)run;
+        blocks = (blocks + 8 * run - 1) / (8 * run) * (8 * run);
         if (blocks > INT32_MAX) return (int)hipErrorInvalidValue;
         if (c.lds > 65536) {   // blocks above 64 KiB of LDS need the limit raised once
             static thread_local std::vector<const void*> raised;

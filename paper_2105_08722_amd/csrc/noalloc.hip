@@ -57,7 +57,7 @@ SliceNeed slice_need(const NpcfPlan& pl, const DevTables* tb, int64_t nprim, int
     auto up = [&](size_t b) { return (std::max<size_t>(b, 256) + align - 1) / align * align; };
     n.bytes = up(alm_row_bytes(pl) * (size_t)n.rows) + up(sizeof(double) * (size_t)n.rows) +
               up(sizeof(double) * (size_t)n.nsplit * (size_t)acc_len(pl, tb)) + up(sizeof(GatherSeg)) +
-              up(sizeof(int32_t) * (size_t)(2 * n.nsplit + 2)) + up(sizeof(double*)) + 2 * up(64);
+              up(sizeof(int32_t) * (size_t)(2 * n.nsplit + 2)) + up(sizeof(double*)) + up(kQueueBytes);
     if (pl.prec == 2) {
         const int64_t nblk = (n.rows + kBlkRows - 1) / kBlkRows;
         n.bytes += up((size_t)nblk * blk_bytes(tb->mf_nent) + 1024);
@@ -121,7 +121,7 @@ extern "C" int encore_npcf_noalloc(encore_ctx* ctx, const encore_grid* grid, int
     if ((rc = tables_in_arena(A, x.s, pl, tb))) return rc;
     const int64_t nprim = primary_subset ? n_subset : grid->g.n;
     if ((rc = ensure(x.prim, sizeof(int32_t) * (size_t)std::max<int64_t>(nprim, 1)))) return rc;
-    if ((rc = ensure(x.misc, sizeof(int64_t) * (size_t)std::max<int64_t>(primary_subset ? n_subset : 0, 1) + 16)))
+    if ((rc = ensure(x.misc, std::max(kPairBytes, sizeof(int64_t) * (size_t)(primary_subset ? n_subset : 0) + 16))))
         return rc;
     int64_t np = 0;
     if ((rc = fill_primaries(x, grid, primary_subset, n_subset, (int32_t*)x.prim.p, &np))) return rc;
@@ -161,7 +161,7 @@ extern "C" int encore_npcf_noalloc(encore_ctx* ctx, const encore_grid* grid, int
         (rc = ensure(x.wprim, sizeof(double) * (size_t)sn.rows)) ||
         (rc = ensure(x.T, sizeof(double) * (size_t)sn.nsplit * (size_t)outs)) ||
         (rc = ensure(x.segs, sizeof(GatherSeg))) || (rc = ensure(x.splits, sizeof(int32_t) * (size_t)(2 * sn.nsplit + 2))) ||
-        (rc = ensure(x.redp, sizeof(double*))) || (rc = ensure(x.queues, 64)))
+        (rc = ensure(x.redp, sizeof(double*))) || (rc = ensure(x.queues, kQueueBytes)))
         return rc;
     if (pl.prec == 2 &&
         (rc = ensure(x.almb, (size_t)((sn.rows + kBlkRows - 1) / kBlkRows) * blk_bytes(tb.mf_nent) + 1024)))

@@ -12,6 +12,7 @@ import numpy as np
 import pytest
 
 import oracle
+import parity_bars as bars
 from paper_2105_08722_amd import encore
 
 pytestmark = pytest.mark.gpu
@@ -63,3 +64,30 @@ def test_accepted_pairs(ctx, precision):
             with encore.build_grid(ctx, pos, w, r_max=edges[-1], box=100.0) as g:
                 encore.npcf(ctx, g, 3, lmax, edges, precision=precision)
             assert ctx.last_timings()["pairs"] == want, (nbins, lmax)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "splitbf16"])
+@pytest.mark.parametrize("lmax", [0, 1, 3, 4, 5, 7, 10])
+def test_persistent_grid_equals_static(ctx, monkeypatch, lmax, precision):
+    """The grid of the gather (one wave per item, or resident waves pulling items)
+    changes no bit of the result and no pair of the count, with one job and with
+    several of uneven size; the result is the oracle's."""
+    print("[groups] grids lmax %d %s" % (lmax, precision), flush=True)
+    pos, w = _catalog()
+    edges = np.linspace(3.0, 28.0, 6)
+    got = []
+    for force in ("0", "1"):
+        monkeypatch.setenv("ENCORE_GATHER_PERSISTENT", force)
+        grids = [encore.build_grid(ctx, pos[:k], w[:k], r_max=edges[-1], box=100.0) for k in (900, 31, 1500)]
+        try:
+            z = encore.npcf_batch(ctx, grids, 3, lmax, edges, precision=precision)
+            pairs = ctx.last_timings()["pairs"]
+            one = encore.npcf(ctx, grids[0], 3, lmax, edges, precision=precision)
+        finally:
+            for g in grids:
+                g.free()
+        assert np.array_equal(one, z[0])
+        got.append((z, pairs))
+    assert np.array_equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
+    zo, za = oracle.zeta(pos[:900], w[:900], 3, lmax, edges, box=100.0, return_abs=True)
+    bars.check(got[0][0][0], zo, za, precision, "lmax %d" % lmax)
