@@ -11,7 +11,7 @@
 //   B[(i, c)][col] = (Re, Im)(w_i a~^{b_K}_{l_K mu}(i)),
 //
 // so that sum_K A B = sum_i w_i Q[P a~].  Rows and columns are grouped in blocks
-// of fixed (mu, beta = b_{K-1}); a block's columns are the bins b_K > beta, so
+// of fixed (mu, parity of l_K, beta = b_{K-1}); a block's columns are the bins b_K > beta, so
 // every computed entry has strictly increasing bins.  The blocks are cut into
 // 16 x 16 output tiles; one wave owns up to four tiles of one block (a "wave
 // job") and forms each of its row operands once per primary.
@@ -61,11 +61,20 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
     P = MfmaPlan();
     P.K = K; P.KF = KF; P.nlm = nlm; P.nbins = nbins; P.nent = nbins * nlm;
 
-    // row keys (rho, q) and column ells per mu
-    std::map<int, std::map<std::vector<int>, int>> rowkeys;   // mu -> key -> index
-    std::map<int, std::map<int, int>> colells;                // mu -> l_K -> index
+    // row keys (rho, q) and column ells per (mu, parity of l_K): a row meets only
+    // columns of one parity (that of its own l sum, or for the Im rows of odd
+    // multiplets the other; 4PCF lmax 5 over 800k primaries 14.3 -> 12.8 ms: 2029
+    // operand tiles formed per K block instead of 2346, 1660 output tiles instead of
+    // 2008).  The 3PCF's few rows (one l each) fill their tiles better together: 501
+    // operand tiles at lmax 10 instead of 875.
+    using Cls = std::pair<int, int>;
+    auto cls = [&](int64_t t) {
+        return Cls(tt.tuple_m[t * K + K - 1], N == 3 ? 0 : tt.tuple_l[t * K + K - 1] & 1);
+    };
+    std::map<Cls, std::map<std::vector<int>, int>> rowkeys;   // class -> key -> index
+    std::map<Cls, std::map<int, int>> colells;                // class -> l_K -> index
     for (int64_t t = 0; t < tt.ntuple; ++t) {
-        const int mu = tt.tuple_m[t * K + K - 1];
+        const Cls mu = cls(t);
         std::vector<int> key;
         for (int k = 0; k < KF; ++k) {
             key.push_back(tt.tuple_l[t * K + k]);
@@ -87,7 +96,7 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
         std::map<std::vector<int>, int> pre_index;
         int nrho = 0, nell = 0;
     };
-    std::map<std::pair<int, int>, BlockInfo> blocks;
+    std::map<std::pair<Cls, int>, BlockInfo> blocks;
     const int W = KF + 1;
     std::vector<std::vector<int32_t>> shape_jobs(kNumMfmaShapes);
     struct JobRef { int shape; int64_t idx; };
@@ -95,7 +104,7 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
     int64_t ntiles = 0;
 
     for (auto& kv : rowkeys) {
-        const int mu = kv.first;
+        const Cls mu = kv.first;
         // Row keys ordered by the factor that takes bin beta (the last row factor),
         // then the rest: consecutive rows of a tile then share that factor, whose
         // LDS read is a broadcast.  The key index is the row key's position here.
@@ -140,7 +149,7 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
             // columns: b_K outer, l_K inner, cut into groups of at most 4 tiles
             std::vector<int32_t> cvals;
             for (int bK = beta + 1; bK < nbins; ++bK)
-                for (int l : ells) cvals.push_back(bK * nlm + lm_of(l, mu));
+                for (int l : ells) cvals.push_back(bK * nlm + lm_of(l, mu.first));
             const int nct_all = (ncol + 15) / 16;
             const int nrt = (nrow + 15) / 16;
             for (int cg = 0; cg * 4 < nct_all; ++cg) {
@@ -179,7 +188,7 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
     const int64_t nB = (int64_t)bt.size() / K;
     P.tmap.assign((size_t)(tt.ntuple * nB), 0);
     for (int64_t t = 0; t < tt.ntuple; ++t) {
-        const int mu = tt.tuple_m[t * K + K - 1];
+        const Cls mu = cls(t);
         std::vector<int> key;
         int neg = 0;
         for (int k = 0; k < KF; ++k) {
@@ -266,8 +275,13 @@ int build_gemm_plan(int N, int lmax, bool allparity, int nbins, int KL, GemmPlan
     P.K = K; P.KL = KL; P.KR = KR; P.nlm = nlm; P.nbins = nbins; P.nent = nbins * nlm;
 
     // row keys (l, m of the first KL factors, Im part) and column keys (l, m of the
-    // rest) by the m-sum s of the row factors
-    std::map<int, std::map<std::vector<int>, int>> rkeys, ckeys;
+    // rest) by the m-sum s of the row factors and the parity of the sum of the column
+    // factors' l: a row meets only columns of one parity (that of its own l sum, or for
+    // the Im rows of odd multiplets the other), so half of an unsplit block's outputs
+    // would belong to no tuple (5PCF lmax 4 over 500k primaries 59 -> 41.5 ms, 6PCF
+    // lmax 3 over 20k 9.5 -> 6.3 ms: 10839 output tiles instead of 20409, 41270 instead
+    // of 78600)
+    std::map<std::pair<int, int>, std::map<std::vector<int>, int>> rkeys, ckeys;
     auto rkey = [&](int64_t t) {
         std::vector<int> k;
         for (int f = 0; f < KL; ++f) { k.push_back(tt.tuple_l[t * K + f]); k.push_back(tt.tuple_m[t * K + f]); }
@@ -279,14 +293,15 @@ int build_gemm_plan(int N, int lmax, bool allparity, int nbins, int KL, GemmPlan
         for (int f = KL; f < K; ++f) { k.push_back(tt.tuple_l[t * K + f]); k.push_back(tt.tuple_m[t * K + f]); }
         return k;
     };
-    auto msum = [&](int64_t t) {
-        int s = 0;
+    auto cls = [&](int64_t t) {
+        int s = 0, l = 0;
         for (int f = 0; f < KL; ++f) s += tt.tuple_m[t * K + f];
-        return s;
+        for (int f = KL; f < K; ++f) l += tt.tuple_l[t * K + f];
+        return std::make_pair(s, l & 1);
     };
     for (int64_t t = 0; t < tt.ntuple; ++t) {
-        rkeys[msum(t)][rkey(t)] = 0;
-        ckeys[msum(t)][ckey(t)] = 0;
+        rkeys[cls(t)][rkey(t)] = 0;
+        ckeys[cls(t)][ckey(t)] = 0;
         if (tt.tuple_odd[t]) P.any_odd = true;
     }
     for (auto& kv : rkeys) { int i = 0; for (auto& e : kv.second) e.second = i++; }
@@ -300,11 +315,25 @@ int build_gemm_plan(int N, int lmax, bool allparity, int nbins, int KL, GemmPlan
         int mr = 0, mc = 0;   // macro tile shape (row tiles, column tiles)
         int nmc = 0;          // macro tiles along the columns
     };
-    std::map<std::pair<int, int>, Block> blocks;
+    // The largest plan accepted: 2^31 outputs in blocks of fixed (s, b_KL) alone, both
+    // parities together.
+    {
+        std::map<int, std::pair<int64_t, int64_t>> keys;   // s -> row and column keys
+        for (auto& kv : rkeys) keys[kv.first.first].first += (int64_t)kv.second.size();
+        for (auto& kv : ckeys) keys[kv.first.first].second += (int64_t)kv.second.size();
+        int64_t tiles = 0;
+        for (auto& kv : keys)
+            for (int beta = KL - 1; beta <= nbins - 1 - KR; ++beta)
+                tiles += (kv.second.first * (int64_t)binomial(beta, KL - 1) + 15) / 16 *
+                         ((kv.second.second * (int64_t)binomial(nbins - 1 - beta, KR) + 15) / 16);
+        if (tiles * 256 > INT32_MAX)
+            return fail(ENCORE_EUNSUPPORTED, "split-bf16 coupling plan too large for this (N, lmax, nbins)");
+    }
+    std::map<std::pair<std::pair<int, int>, int>, Block> blocks;
     const int RW = KL + 1, CW = KR + 1;
     int64_t ntiles = 0;
     for (auto& kv : rkeys) {
-        const int s = kv.first;
+        const std::pair<int, int> s = kv.first;
         if (!ckeys.count(s)) continue;
         const auto& rk = kv.second;
         const auto& ck = ckeys[s];
@@ -380,7 +409,7 @@ int build_gemm_plan(int N, int lmax, bool allparity, int nbins, int KL, GemmPlan
     const int64_t nB = (int64_t)bt.size() / K;
     P.tmap.assign((size_t)(tt.ntuple * nB), 0);
     for (int64_t t = 0; t < tt.ntuple; ++t) {
-        const int s = msum(t);
+        const std::pair<int, int> s = cls(t);
         const int rho = rkeys[s][rkey(t)], sig = ckeys[s][ckey(t)];
         int neg = 0;
         for (int f = 0; f < K; ++f) {

@@ -34,7 +34,8 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P);
 // after the first KL: rows are the products of the first KL factors (their (l, m),
 // the Re or Im part, the bins b_1 < .. < b_KL), columns w times the products of
 // the other KR = K - KL factors (their (l, m), bins b_KL < b_{KL+1} < .. < b_K).
-// Rows and columns are grouped in blocks of fixed (sum of the row factors' m, b_KL):
+// Rows and columns are grouped in blocks of fixed (sum of the row factors' m, parity
+// of the sum of the column factors' l, b_KL):
 // a tuple's row and column meet only inside its block.  Each block is cut into
 // macro tiles of MR x MC 16 x 16 output tiles, MR + MC <= kGemmMaxOps and at most
 // kGemmMaxOps blocks of 2 x 2 output tiles (ceil(MR/2) ceil(MC/2)); one workgroup
