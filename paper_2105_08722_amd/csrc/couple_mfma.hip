@@ -338,12 +338,11 @@ int launch_shape(const MfmaArgs& a, hipStream_t stream)
 }
 
 // ---------------------------------------------------------------- macro-tiled GEMM
-// One workgroup per (split, macro tile) of the GEMM plan (mfma_plan.h).  Wave k
-// forms operand tile k of the macro tile (its row tiles first: products of the
-// first KL factors, Re or Im part; then its column tiles: w times the products of
-// the other KR factors), split into bf16 hi + lo and stored in LDS in the MFMA lane
-// order; wave w computes one 2 x 2 block of output tiles (three MFMAs each) from
-// the shared operands, reading each of its two row and two column operand tiles
+// One workgroup per (split, pack of macro tiles) of the GEMM plan (mfma_plan.h).  Each
+// wave forms one operand tile (a row tile: products of the first KL factors, Re or Im
+// part; or a column tile: w times the products of the other KR factors), split into
+// bf16 hi + lo and stored in LDS in the MFMA lane order; and computes one 2 x 2 block
+// of output tiles (three MFMAs each) from the shared operands, reading each of its two row and two column operand tiles
 // once per K block.  The two are pipelined over two operand buffers: in one step a
 // wave issues the MFMAs of K block st and forms its operand of K block st + 1, so
 // one barrier per K block separates them.
@@ -397,13 +396,13 @@ __global__ void __launch_bounds__(kGmThreads) k_couple_gemm(MfmaArgs a)
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x & (kWave - 1);
     const int g = lane >> 4, c16 = lane & 15;
-    const int32_t* M = a.jobs + (size_t)mac * kGemmMacroWidth;
-    const int row_start = M[0], col_start = M[1], MR = M[2], MC = M[3], tile_base = M[4];
+    const int32_t* M = a.jobs + (size_t)mac * kGemmPackWidth + wid * kGemmPackWave;
+    const int op_start = M[0], op_kind = M[1], slots = M[2], shape = M[3], tile0 = M[4];
 
-    // formation role: operand tile wid (row tile wid, or column tile wid - MR).
-    // Padding rows and columns read real entries; their outputs are never mapped.
-    const bool forms = wid < MR + MC;
-    const bool is_col = wid >= MR;
+    // formation role: operand tile wid.  Padding rows and columns read real entries;
+    // their outputs are never mapped.
+    const bool forms = op_kind >= 0;
+    const bool is_col = op_kind == 1;
     int roff[KL], coff[KR];
     unsigned fl = 0;
 #pragma unroll
@@ -412,30 +411,23 @@ __global__ void __launch_bounds__(kGmThreads) k_couple_gemm(MfmaArgs a)
     for (int k = 0; k < KR; ++k) coff[k] = 32 * g;
     if (forms) {
         if (is_col) {
-            const int32_t* c = a.cols + (size_t)(col_start + 16 * (wid - MR) + c16) * (KR + 1);
+            const int32_t* c = a.cols + (size_t)(op_start + c16) * (KR + 1);
 #pragma unroll
             for (int k = 0; k < KR; ++k) coff[k] = c[k] * kEntBytes + 32 * g;
             fl = (unsigned)c[KR];
         } else {
-            const int32_t* r = a.rows + (size_t)(row_start + 16 * wid + c16) * (KL + 1);
+            const int32_t* r = a.rows + (size_t)(op_start + c16) * (KL + 1);
 #pragma unroll
             for (int k = 0; k < KL; ++k) roff[k] = r[k] * kEntBytes + 32 * g;
             fl = (unsigned)r[KL];
         }
     }
-    // output role: the 2 x 2 block (bi, bj) of output tiles, rows tr0, tr0 + 1 and
-    // columns tc0, tc0 + 1 of the macro tile, those inside it (wave-uniform)
-    const int nbc = (MC + 1) / 2;
-    const int bi = wid / nbc, bj = wid - bi * nbc;
-    const int tr0 = 2 * bi, tc0 = 2 * bj;
-    const int nr = bi < (MR + 1) / 2 ? min(2, MR - tr0) : 0;   // 0: no block for this wave
-    const int nc = min(2, MC - tc0);
-    // operand slots of the block's rows and columns; a row or column outside the
-    // macro tile (and every operand of a wave without a block) reads a real operand
-    // tile, and the tiles it feeds are never written
-    const int r0 = nr > 0 ? tr0 : 0, c0 = nr > 0 ? tc0 : 0;
-    const int aslot[2] = {r0 * kOpBytes + lane * 16, (nr == 2 ? r0 + 1 : r0) * kOpBytes + lane * 16};
-    const int bslot[2] = {(MR + c0) * kOpBytes + lane * 16, (MR + (nc == 2 ? c0 + 1 : c0)) * kOpBytes + lane * 16};
+    // output role: a block of nr x nc output tiles from the operand tiles of two (or
+    // one, named twice) row slots and column slots; a wave without a block (nr = 0)
+    // reads slot 0 and writes nothing
+    const int nr = shape & 0xff, nc = (shape >> 8) & 0xff, MC = shape >> 16;
+    const int aslot[2] = {(slots & 0xff) * kOpBytes + lane * 16, ((slots >> 8) & 0xff) * kOpBytes + lane * 16};
+    const int bslot[2] = {((slots >> 16) & 0xff) * kOpBytes + lane * 16, ((slots >> 24) & 0xff) * kOpBytes + lane * 16};
 
     f32x4 acc[2][2];
     double acc64[2][2][4];
@@ -551,7 +543,7 @@ __global__ void __launch_bounds__(kGmThreads) k_couple_gemm(MfmaArgs a)
         if constexpr (!GL) copy_block(st + ST);
         const unsigned char* ob = opnd + (size_t)(st & 1) * kGmOpnd;
         // the block's row and column operands, each read once, and the MFMAs of its
-        // tiles inside the macro tile
+        // tiles
         auto products = [&]() {
             if (nr == 0) return;                          // wave-uniform
             u32x4 ah[2], al[2], bh[2], bl[2];
@@ -596,13 +588,13 @@ __global__ void __launch_bounds__(kGmThreads) k_couple_gemm(MfmaArgs a)
     // no copy may still be writing LDS when the block ends
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // output tile layout of the 16x16 MFMA: lane holds column c16, rows 4g .. 4g+3
-    double* D = a.D + (size_t)split * a.dense + (size_t)tile_base * 256;
+    double* D = a.D + (size_t)split * a.dense + (size_t)tile0 * 256;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            if (i >= nr || j >= nc) continue;              // never written: outside the macro tile
-            double* t = D + (size_t)((tr0 + i) * MC + tc0 + j) * 256;
+            if (i >= nr || j >= nc) continue;              // no such tile
+            double* t = D + (size_t)(i * MC + j) * 256;
 #pragma unroll
             for (int r = 0; r < 4; ++r) t[(4 * g + r) * 16 + c16] = acc64[i][j][r];
         }

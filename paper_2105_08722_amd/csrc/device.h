@@ -193,7 +193,7 @@ struct MfmaArgs {
 };
 int launch_couple_mfma(const MfmaArgs& a, int KF, int shape, hipStream_t stream);
 // The macro-tiled GEMM of a GemmPlan (mfma_plan.h): rows / cols hold the plan's rows
-// and columns, jobs its macro tiles (njobs of them), KL + KR factors.
+// and columns, jobs its packs of macro tiles (njobs of them), KL + KR factors.
 int launch_couple_gemm(const MfmaArgs& a, int KL, int KR, hipStream_t stream);
 
 // Edge correction: builds the coupling matrices of bin tuples [B_lo, B_lo + nb) from

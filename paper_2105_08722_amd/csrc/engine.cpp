@@ -258,12 +258,12 @@ static int fill_mfma(DevTables& d, const NpcfPlan& pl, Up&& up)
         GemmPlan G;
         if ((rc = build_gemm_plan(pl.N, pl.lmax, pl.allparity, pl.nbins, gemm_split(pl.N), G))) return rc;
         if ((rc = up(d.mf_rows, G.rows)) || (rc = up(d.mf_cols, G.cols)) || (rc = up(d.mf_tmap, G.tmap)) ||
-            (rc = up(d.mf_macros, G.macros)))
+            (rc = up(d.mf_packs, G.packs)))
             return rc;
         d.mf_gemm = true;
         d.mf_KL = G.KL;
         d.mf_KR = G.KR;
-        d.mf_nmacro = (int)(G.macros.size() / kGemmMacroWidth);
+        d.mf_npack = (int)(G.packs.size() / kGemmPackWidth);
         d.mf_any_odd = G.any_odd;
         d.mf_nent = G.nent;
         d.mf_dense = G.ntiles * 256;
@@ -391,7 +391,7 @@ int64_t job_split_rows(const NpcfPlan& pl, const DevTables* tb, int64_t nprim, i
         // MFMA coupling: one block per (split, 16 wave jobs or one macro tile); aim
         // at ~2048 blocks
         int64_t nbj = 0;
-        if (tb->mf_gemm) nbj = tb->mf_nmacro;
+        if (tb->mf_gemm) nbj = tb->mf_npack;
         else
             for (int sh = 0; sh < kNumMfmaShapes; ++sh) nbj += (tb->mf_njobs[sh] + 15) / 16;
         // The launch runs splits in whole groups of 8 one per XCD (the blocks of a
@@ -526,8 +526,8 @@ int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl
     ma.dense = tb->mf_dense;
     ma.any_odd = pl.allparity ? 1 : 0;
     if (tb->mf_gemm) {
-        ma.jobs = tb->mf_macros;
-        ma.njobs = tb->mf_nmacro;
+        ma.jobs = tb->mf_packs;
+        ma.njobs = tb->mf_npack;
         ma.any_odd = tb->mf_any_odd ? 1 : 0;
     }
 

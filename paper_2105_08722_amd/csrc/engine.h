@@ -45,11 +45,11 @@ struct DevTables {
     int mf_njobs[kNumMfmaShapes] = {0, 0, 0, 0};
     int32_t* mf_tmap = nullptr;
     // macro-tiled GEMM plan (used instead of the wave jobs when mf_gemm): mf_rows /
-    // mf_cols hold its rows and columns, mf_macros its macro tiles
+    // mf_cols hold its rows and columns, mf_packs its macro tiles by workgroup
     bool mf_gemm = false;
-    int mf_KL = 0, mf_KR = 0, mf_nmacro = 0;
+    int mf_KL = 0, mf_KR = 0, mf_npack = 0;
     bool mf_any_odd = false;
-    int32_t* mf_macros = nullptr;
+    int32_t* mf_packs = nullptr;
 };
 // whether the split-BF16 coupling of N runs as the macro-tiled GEMM
 bool use_gemm_coupling(int N);

@@ -38,19 +38,30 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P);
 // of the sum of the column factors' l, b_KL):
 // a tuple's row and column meet only inside its block.  Each block is cut into
 // macro tiles of MR x MC 16 x 16 output tiles, MR + MC <= kGemmMaxOps and at most
-// kGemmMaxOps blocks of 2 x 2 output tiles (ceil(MR/2) ceil(MC/2)); one workgroup
-// forms a macro tile's MR + MC operand tiles once per 16 primaries and computes all
-// its output tiles from them, one 2 x 2 block per wave.  The shape is chosen per
+// kGemmMaxOps blocks of 2 x 2 output tiles (ceil(MR/2) ceil(MC/2)); a workgroup takes
+// as many macro tiles as fit its waves, forms their MR + MC operand tiles once per 16
+// primaries, one per wave, and computes all their output tiles from them, one 2 x 2
+// block per wave.  The shape is chosen per
 // block: thin blocks (few row tiles) take long macro tiles, so that their row
 // operands are formed fewer times.
 constexpr int kGemmMaxOps = 16;      // operand tiles of a macro tile (one per wave)
 constexpr int kGemmMacroWidth = 5;   // row_start, col_start, row tiles, column tiles, tile_base
+// One workgroup's work: macro tiles whose operand tiles and 2 x 2 output blocks fit its
+// kGemmMaxOps waves together.  For each wave w, at [kGemmPackWave * w]:
+//   0: the first row (kind 0) or column (kind 1) of the operand tile that it forms
+//   1: its kind, -1: none
+//   2: operand slots (waves) of its output block: rows 0, 1 and columns 0, 1, 8 bits each
+//   3: rows | columns << 8 (1 or 2 each; 0: no block) | column tiles of the macro << 16
+//   4: tile index of the block's first tile
+constexpr int kGemmPackWave = 5;
+constexpr int kGemmPackWidth = kGemmPackWave * kGemmMaxOps;
 struct GemmPlan {
     int K = 0, KL = 0, KR = 0, nlm = 0, nbins = 0, nent = 0;
     bool any_odd = false;
     std::vector<int32_t> rows;     // [nrow][KL + 1]: entries (bin * nlm + lm of |m|), flags
     std::vector<int32_t> cols;     // [ncol][KR + 1]: entries, flags
     std::vector<int32_t> macros;   // [nmacro][kGemmMacroWidth]
+    std::vector<int32_t> packs;    // [npack][kGemmPackWidth]: the macro tiles by workgroup
     std::vector<int32_t> blocks;   // [nblock][2]: row tiles, column tiles of each block
     int64_t ntiles = 0;
     std::vector<int32_t> tmap;     // [ntuple * nB], as MfmaPlan::tmap
