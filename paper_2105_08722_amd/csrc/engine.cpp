@@ -552,12 +552,13 @@ int launch_slice_gather(const SliceLaunch& L, const NpcfPlan& pl, hipStream_t s)
     return ENCORE_OK;
 }
 
-int launch_slice_couple(const SliceLaunch& L, const NpcfPlan& pl, const DevTables* tb, hipStream_t s)
+int launch_slice_couple(const SliceLaunch& L, const NpcfPlan& pl, const DevTables* tb, hipStream_t s, bool blocked)
 {
     if (L.rows == 0) return ENCORE_OK;
     if (pl.prec == 2) {
-        HIPTRY((hipError_t)launch_to_blocked((const float2*)L.ga.alm, L.ga.wprim, L.ga.segs, L.ga.nseg,
-                                             (int)L.rows, L.ma.nent, (float*)L.ma.alm, s));
+        if (!blocked)
+            HIPTRY((hipError_t)launch_to_blocked((const float2*)L.ga.alm, L.ga.wprim, L.ga.segs, L.ga.nseg,
+                                                 (int)L.rows, L.ma.nent, (float*)L.ma.alm, s));
         if (tb->mf_gemm) {
             HIPTRY((hipError_t)launch_couple_gemm(L.ma, tb->mf_KL, tb->mf_KR, s));
         } else {

@@ -178,7 +178,9 @@ struct SliceLaunch {
 int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl, const DevTables* tb,
                   const double* edges, const std::vector<Chunk>& chunks, SliceLaunch& L);
 int launch_slice_gather(const SliceLaunch& L, const NpcfPlan& pl, hipStream_t s);
-int launch_slice_couple(const SliceLaunch& L, const NpcfPlan& pl, const DevTables* tb, hipStream_t s);
+// blocked: the split-BF16 coupling's blocked copy is there already
+int launch_slice_couple(const SliceLaunch& L, const NpcfPlan& pl, const DevTables* tb, hipStream_t s,
+                        bool blocked = false);
 // zeta[nlam][nB] (device) from a job's T (device); bscale[nB] (device) or null.
 int contract_job(Exec& x, const NpcfPlan& pl, const DevTables* tb, const double* T,
                  const double* bscale, double* zeta);

@@ -133,3 +133,21 @@ def test_mesh_rejects_bad_arguments(ctx):
         encore.npcf_mesh(ctx, delta.float(), 8.0, 3, 2, np.array([1.0, 2.0, 3.0]))
     z = encore.npcf_mesh(ctx, delta, 8.0, 3, 2, np.array([1.0, 2.0, 3.0]))       # empty field
     assert np.all(z == 0.0)
+
+
+@pytest.mark.parametrize("N,lmax,n,nbins", [
+    (3, 0, 6, 2),      # 216 cells: 13.5 blocks of 16 rows, 2 fields (a block holds 4 entries)
+    (4, 2, 9, 3),      # 729 cells: 45.6 blocks, 18 fields (one tile of 16 and 2)
+    (3, 2, 7, 5),      # 343 cells, 30 fields
+    (4, 4, 12, 3),     # 1728 cells: whole tiles of 64 rows, 45 fields
+])
+def test_mesh_splitbf16_ragged_blocks(ctx, N, lmax, n, nbins):
+    """Cell counts and field counts off the tiles of the blocked layout's writer."""
+    import torch
+    L = float(n)
+    edges = np.linspace(0.8, 0.46 * n, nbins + 1) + 0.013
+    delta = synth.mesh_counts(*_catalog(500, n, L, 5 * N + n), n, L)
+    zg = encore.npcf_mesh(ctx, torch.from_numpy(delta).cuda(), L, N, lmax, edges, precision="splitbf16")
+    zo, za = omesh.mesh_zeta(delta, L, N, lmax, edges, return_abs=True)
+    e, _ = bars.check(zg, zo, za, "splitbf16", "ragged mesh")
+    _say("ragged mesh N=%d lmax=%d n=%d bins=%d: max e_L = %.2e" % (N, lmax, n, nbins, e))
