@@ -134,11 +134,15 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
             for (const auto* key : keys)
                 for (const auto& pre : pres) {
                     int flags = 1 << 9;   // valid
-                    for (int k = 0; k < KF; ++k) {
+                    // a single conjugated factor of two comes second (the kernel
+                    // conjugates the second, or both)
+                    const bool swap = KF == 2 && (*key)[1] < 0 && (*key)[3] >= 0;
+                    for (int i = 0; i < KF; ++i) {
+                        const int k = swap ? KF - 1 - i : i;
                         const int l = (*key)[2 * k], m = (*key)[2 * k + 1];
                         const int bin = (k < KF - 1) ? pre[k] : beta;
                         P.rows.push_back(bin * nlm + lm_of(l, std::abs(m)));
-                        if (m < 0) flags |= 1 << k;
+                        if (m < 0) flags |= 1 << i;
                     }
                     if ((*key)[2 * KF]) flags |= 1 << 8;
                     P.rows.push_back(flags);
