@@ -573,9 +573,9 @@ __global__ void __launch_bounds__(kGmThreads) k_couple_gemm(MfmaArgs a)
             if (st + 2 < nstep) form(st + 1, std::false_type{});   // inside the split
             else form(st + 1, std::true_type{});                  // the split's last K block
         };
-        // (half the waves taking the forming first, so that one SIMD's matrix core
-        // and VALU would overlap after the barrier, measured slower: 100 ms against
-        // 86 ms for the 6PCF at lmax 3 over 200k primaries)
+        // (Slower: half the waves forming first, so that one SIMD's matrix core and VALU
+        // would overlap after the barrier, by 16%; reading the next factors before the
+        // MFMAs, by 10%; 8 waves of 4 x 3 output tiles over 24 operand tiles, by 5%.)
         products();
         next();
         if ((st + 1) % kFlushSteps == 0 || st + 1 == nstep) {

@@ -49,9 +49,9 @@ constexpr int kSegPerRow = 6;      // <= 2 x-ranges x 3 periodic images
 constexpr int kSegCap = kRowsPerBatch * kSegPerRow;
 // One wave per workgroup: its registers and LDS are free for the next item as soon as
 // it ends.  Four waves of consecutive rows per workgroup, which shared one compute
-// unit's vector L1, waited for their slowest (5PCF-like primaries, a random 20,000 of a
-// 200k-point wedge, lmax 5, ms, 4 waves / 1 wave: FP32 2.88 / 2.44, FP64 5.54 / 4.68;
-// every primary of a 100k-point box 6.77 / 6.84 and 13.07 / 12.34).
+// unit's vector L1, waited for their slowest (a random 20,000 primaries of a 200k-point
+// wedge, lmax 5, FP32: 4 waves 2.88 ms, 1 wave 2.44, FP64 18% more with 4; every primary
+// of a 100k-point box 6.77 / 6.84 ms, FP64 6% more with 4).
 constexpr int kWavesPerBlock = 1;
 constexpr int kRedCh = 16;         // accumulator values per pass of the lane reduction
 
@@ -936,9 +936,9 @@ const void* kfn() { return reinterpret_cast<const void*>(&k_gather<T, L, NBG, M0
 // PERSOK: also as a persistent kernel.  Its item loop holds about 15 more registers:
 // where that costs a resident wave (FP64 and FP32-path accumulators at lmax 4 and 6),
 // and in FP64 from lmax 4 on, where the item's own arithmetic dominates, the static grid
-// is as fast or faster (ms, static / persistent, over 100k points: lmax 4 FP64 9.4 /
-// 11.5, FP32 path 7.8 / 9.6; lmax 5 FP64 12.3 / 12.9; the dense random splits of 16
-// catalogs in FP64 24.3 / 24.9).
+// is as fast or faster (over 100k points the persistent one takes 22% more in FP64 and
+// 23% more on the FP32 path at lmax 4, 5% more in FP64 at lmax 5; over dense random
+// splits in FP64 2% more).
 template <typename T, int L, int NBG, bool COMP = false, bool PERSOK = true>
 KernelCfg cfg1()
 {
@@ -968,8 +968,8 @@ KernelCfg cfg2()
 // best or within 3% of best wherever their accumulators fit (4PCF gather, 200k
 // points at the benchmark density / 50k primaries of the survey wedge, ms: lmax 3
 // FP32 2 bins 12.4 / 5.8, 3 bins 13.4 / 6.8, 4 bins 12.7 / 6.5; lmax 4 FP32 2 bins
-// 12.3 / 6.2, 3 bins 14.6 / 7.3; FP64 lmax 3 2 bins 16.7, 5 bins 33.5, lmax 4 2 bins
-// 18.3, 3 bins 24.3); at lmax 0 and 1 four bins win without clustering (11.3 against
+// 12.3 / 6.2, 3 bins 14.6 / 7.3; FP64 at lmax 3 twice the time with 5 bins, at lmax 4 a
+// third more with 3 and 15% more with 1); at lmax 0 and 1 four bins win without clustering (11.3 against
 // 12.2) and lose on the wedge (5.8 against 5.1), so both are compiled and
 // encore_autotune picks one per job shape (ENCORE_GATHER_NBG overrides).
 int nbg_env()
@@ -1122,7 +1122,7 @@ int launch_gather(const GatherArgs& a0, int lmax, int precision, int nbg, int gr
         }
         // runs of at most 1024 items per XCD, 16 runs each or more: with one contiguous
         // eighth of the items per XCD those of sparse regions were idle at the end
-        // (dense random splits, FP64: 27.5 -> 24.3 ms)
+        // (dense random splits in FP64: 12% less time)
         int64_t run = 1;
         while (run < 1024 && 256 * run <= blocks) run *= 2;
         a.xcd_run = (int)run;
