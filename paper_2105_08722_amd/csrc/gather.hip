@@ -779,7 +779,8 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
         wave_sync();
     }
 
-    if (a.npairs && lane == 0) {
+    // (of the kernels over parts of the m range, which scan the same pairs, one counts)
+    if (M0 == 0 && a.npairs && lane == 0) {
         unsigned long long tot = pairs;
 #pragma unroll
         for (int k = 0; k < NBG; ++k) tot += (unsigned long long)(top[k] - k * kCap);
