@@ -97,21 +97,22 @@ __global__ void __launch_bounds__(kBlock) k_couple(CoupleArgs a, int ptile)
 // thread loads a~^{b1} of its first factor, the second factor's a~^{b2} and the third
 // factor's a~^{b3} once each, forms P = w a1 a2 once per b2 and adds Q[P a3] for every
 // b3 > b2: about one product per output and primary instead of k_couple's three.
-// TI: the coefficients' type, TC: that of the products.  TC = double adds to the FP64
-// sums directly; TC = float (the FP32 path at 10 bins) to FP32 sums over a tile of
-// primaries, then to FP64 sums.  Bound by FP64 issue and the LDS reads alike at b1 = 0
-// (17 reads of 16 bytes for 104 multiply-adds).  Without the FP32 path's second set of
-// sums, which the FP64 path used to keep too, and with several b1 per launch, 10 bins
-// at lmax 5 over 60k primaries take 2.52 ms in FP64 (3.55 before).
+// TI: the coefficients' type, TC: that of the products.  TILED (10 bins): the sums over a
+// tile of primaries are added to the FP64 sums, so that a split's thousands of terms are
+// not rounded one by one at the size of their sum; otherwise the terms are added to
+// the FP64 sums directly.  Bound by FP64 issue
+// and the LDS reads alike at b1 = 0 (17 reads of 16 bytes for 104 multiply-adds).  With
+// the products as multiply-adds into the sums, and several b1 per launch, 10 bins at
+// lmax 5 over 60k primaries take 2.96 ms in FP64 (3.53 with products, then sums; 2.53
+// without tiles, whose sums round 2 to 3 times as much).
 constexpr int kNB4 = 10;
 constexpr int kNB4Max = 12;   // its 55 FP64 sums and 2 x 12 coefficients per thread fit the registers
 __host__ __device__ constexpr int pair_count(int nr) { return (nr - 1) * (nr - 2) / 2; }   // b1 < b2 < b3 of nr bins
 
-template <typename TI, typename TC, int NR>
+template <typename TI, typename TC, bool TILED, int NR>
 __device__ __forceinline__ void couple4_bins(const CoupleArgs& a, int ptile, int t, unsigned char* smem)
 {
     using V = typename C2<TI>::type;
-    constexpr bool TILED = sizeof(TC) == 4;
     constexpr int NA = pair_count(NR);
     const int B1 = a.nbins - NR;
     V* tile = reinterpret_cast<V*>(smem);
@@ -177,7 +178,8 @@ __device__ __forceinline__ void couple4_bins(const CoupleArgs& a, int ptile, int
                     if (take_im) { const TC tmp = pr; pr = pi; pi = -tmp; }   // Im(z) = Re(-i z)
 #pragma unroll
                     for (int b3 = b2 + 1; b3 < NR; ++b3) {
-                        if constexpr (TILED) part[q] += pr * u3r[b3] - pi * u3i[b3];
+                        if constexpr (sizeof(TC) == 4) part[q] += pr * u3r[b3] - pi * u3i[b3];
+                        else if constexpr (TILED) part[q] = fma(-pi, u3i[b3], fma(pr, u3r[b3], part[q]));
                         else acc[q] = fma(-pi, u3i[b3], fma(pr, u3r[b3], acc[q]));
                         ++q;
                     }
@@ -201,7 +203,7 @@ __device__ __forceinline__ void couple4_bins(const CoupleArgs& a, int ptile, int
 
 // the first bins b1 = nbins - nr of nr = NRLO .. NRHI, the one with the most tuples of
 // bins first
-template <typename TI, typename TC, int NRLO, int NRHI>
+template <typename TI, typename TC, bool TILED, int NRLO, int NRHI>
 __global__ void __launch_bounds__(kBlock) k_couple4(CoupleArgs a, int ptile, int tblocks, int nr_first)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -209,7 +211,7 @@ __global__ void __launch_bounds__(kBlock) k_couple4(CoupleArgs a, int ptile, int
     const int t = (blockIdx.x - j * tblocks) * kBlock + threadIdx.x;
     const int nr = nr_first - j;                          // uniform over the block
     [&]<int... R>(std::integer_sequence<int, R...>) {
-        ((nr == R + NRLO ? couple4_bins<TI, TC, R + NRLO>(a, ptile, t, smem) : (void)0), ...);
+        ((nr == R + NRLO ? couple4_bins<TI, TC, TILED, R + NRLO>(a, ptile, t, smem) : (void)0), ...);
     }(std::make_integer_sequence<int, NRHI - NRLO + 1>{});
 }
 
@@ -293,7 +295,7 @@ int couple_ptile(int nbins, int nlm, int precision)
     return pt < 1 ? 1 : (pt > 64 ? 64 : pt);
 }
 
-template <typename TI, typename TC, int NRLO, int NRHI>
+template <typename TI, typename TC, bool TILED, int NRLO, int NRHI>
 int launch4(const CoupleArgs& a, hipStream_t stream)
 {
     const int hi = std::min(NRHI, a.nbins);
@@ -301,29 +303,33 @@ int launch4(const CoupleArgs& a, hipStream_t stream)
     const int ptile = std::max(1, std::min(64, 32768 / (a.nbins * a.nlm * (int)sizeof(typename C2<TI>::type) + 8)));
     const int tblocks = (a.ntuple + kBlock - 1) / kBlock;
     const size_t lds = (size_t)ptile * hi * a.nlm * sizeof(typename C2<TI>::type) + 8 * (size_t)ptile;
-    k_couple4<TI, TC, NRLO, NRHI><<<dim3((unsigned)(tblocks * (hi - NRLO + 1)), (unsigned)a.nsplit), kBlock, lds,
+    k_couple4<TI, TC, TILED, NRLO, NRHI><<<dim3((unsigned)(tblocks * (hi - NRLO + 1)), (unsigned)a.nsplit), kBlock, lds,
                                     stream>>>(a, ptile, tblocks, hi);
     return (int)hipGetLastError();
 }
 
 // Several first bins share a launch so that no launch's end leaves the chip idle for
-// long; the register use of a launch is that of its largest, which keeps the small
-// ones apart where there are enough blocks (4PCF lmax 5, 60k primaries, ms, one launch
-// per b1 / these groups / one launch: FP64 10 bins 2.79 / 2.52 / 2.76, 8 bins 1.86 /
-// 1.63 / 1.57, 12 bins 12.8 / 6.3 / 5.6; FP32 10 bins with {8..10} in one launch 2.30,
-// {10} alone 2.07).
-template <typename TI>
-int launch4_fp64(const CoupleArgs& a, hipStream_t stream)
+// long; the register use of a launch is that of its largest, which keeps the largest
+// apart at 10 bins (4PCF lmax 5, 60k primaries, ms: FP64 {8..10} in one launch 3.08, {10}
+// alone 2.96; FP32 2.30, 2.07).
+int launch4_tiled(const CoupleArgs& a, hipStream_t stream)   // FP64, 10 bins
 {
-    if (a.nbins > kNB4) return launch4<TI, double, 3, kNB4Max>(a, stream);
-    const int rc = launch4<TI, double, 8, kNB4>(a, stream);
-    return rc != (int)hipSuccess ? rc : launch4<TI, double, 3, 7>(a, stream);
+    int rc = launch4<double, double, true, kNB4, kNB4>(a, stream);
+    if (rc == (int)hipSuccess) rc = launch4<double, double, true, 8, 9>(a, stream);
+    return rc != (int)hipSuccess ? rc : launch4<double, double, true, 3, 7>(a, stream);
+}
+template <typename TI>
+int launch4_fp64(const CoupleArgs& a, hipStream_t stream)    // other bin counts
+{
+    if (a.nbins > kNB4) return launch4<TI, double, false, 3, kNB4Max>(a, stream);
+    const int rc = launch4<TI, double, false, 8, kNB4 - 1>(a, stream);
+    return rc != (int)hipSuccess ? rc : launch4<TI, double, false, 3, 7>(a, stream);
 }
 int launch4_fp32(const CoupleArgs& a, hipStream_t stream)
 {
-    int rc = launch4<float, float, kNB4, kNB4>(a, stream);
-    if (rc == (int)hipSuccess) rc = launch4<float, float, 8, 9>(a, stream);
-    return rc != (int)hipSuccess ? rc : launch4<float, float, 3, 7>(a, stream);
+    int rc = launch4<float, float, true, kNB4, kNB4>(a, stream);
+    if (rc == (int)hipSuccess) rc = launch4<float, float, true, 8, 9>(a, stream);
+    return rc != (int)hipSuccess ? rc : launch4<float, float, true, 3, 7>(a, stream);
 }
 
 int launch_couple(const CoupleArgs& a, int precision, hipStream_t stream)
@@ -331,9 +337,12 @@ int launch_couple(const CoupleArgs& a, int precision, hipStream_t stream)
     if (a.nk > kMaxK) return (int)hipErrorInvalidValue;
     if (a.nsplit == 0 || a.ntuple == 0) return (int)hipSuccess;
     if (use_couple4(a.nk, a.nbins, a.ntuple, a.nB)) {
-        if (precision == 0) return launch4_fp64<double>(a, stream);
-        // the FP32 products of 10 bins are summed in FP32 over a tile of primaries;
-        // other bin counts keep FP64 sums throughout, as in k_couple
+        if (precision == 0)
+            return a.nbins == kNB4 ? launch4_tiled(a, stream) : launch4_fp64<double>(a, stream);
+        // the FP32 products of 10 bins are summed in FP32 over a tile of primaries; at
+        // other bin counts, where k_couple added each FP32 product to an FP64 sum, the
+        // products are formed in FP64 too: a conversion and an addition in FP64 for each
+        // FP32 product would issue as long as the two FP64 multiply-adds
         return a.nbins == kNB4 ? launch4_fp32(a, stream) : launch4_fp64<float>(a, stream);
     }
     const int64_t nthreads = (int64_t)a.ntuple * a.nB;
