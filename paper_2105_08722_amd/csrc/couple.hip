@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <utility>
 
 #include "device.h"
@@ -100,7 +101,7 @@ __global__ void __launch_bounds__(kBlock) k_couple(CoupleArgs a, int ptile)
 // TI: the coefficients' type, TC: that of the products.  TILED (10 bins): the sums over a
 // tile of primaries are added to the FP64 sums, so that a split's thousands of terms are
 // not rounded one by one at the size of their sum; otherwise the terms are added to
-// the FP64 sums directly.  Bound by FP64 issue
+// the FP64 sums directly, over splits shorter than k_couple's.  Bound by FP64 issue
 // and the LDS reads alike at b1 = 0 (17 reads of 16 bytes for 104 multiply-adds).  With
 // the products as multiply-adds into the sums, and several b1 per launch, 10 bins at
 // lmax 5 over 60k primaries take 2.96 ms in FP64 (3.53 with products, then sums; 2.53
@@ -241,10 +242,10 @@ __global__ void __launch_bounds__(kBlock) k_contract(ContractArgs a)
 }  // namespace
 
 // k_couple4 couples this job: up to 12 bins, and with enough tuples that its blocks,
-// whose lanes are tuples, are not mostly idle (4PCF FP64, 60k primaries, k_couple /
-// k_couple4 in ms: lmax 3 6 bins 0.27 / 0.39, 8 bins 0.65 / 0.51; lmax 5 6 bins 1.52 /
-// 0.80, 8 bins 5.0 / 1.6, 12 bins 25.1 / 5.6).  10 bins always, where k_couple took
-// longer at every lmax.
+// whose lanes are tuples, are not mostly idle (4PCF, 60k primaries, k_couple / k_couple4
+// in ms: FP64 lmax 3 8 bins 0.64 / 0.39, lmax 5 8 bins 5.0 / 1.45, 12 bins 25.1 / 5.5;
+// FP32 path lmax 4 6 bins 0.56 / 0.49).  10 bins always, where k_couple took longer at
+// every lmax.
 static bool use_couple4(int nk, int nbins, int64_t ntuple, int64_t nB)
 {
     return nk == 3 && nbins >= 3 &&
@@ -253,19 +254,24 @@ static bool use_couple4(int nk, int nbins, int64_t ntuple, int64_t nB)
 
 int couple_split_rows(int nk, int nbins, int64_t ntuple, int64_t nB, int64_t nrows)
 {
-    int64_t ns;
-    if (use_couple4(nk, nbins, ntuple, nB)) {
-        // one block per (b1, 256 tuples, split): aim at ~1024 blocks per b1
-        const int64_t tblocks = (ntuple + kBlock - 1) / kBlock;
-        ns = (1024 + tblocks - 1) / std::max<int64_t>(tblocks, 1);
-        // other bin counts keep their partial sums within 64 MiB
-        if (nbins != kNB4) ns = std::min<int64_t>(ns, ((int64_t)64 << 20) / (8 * ntuple * nB));
-    } else {
-        ns = (int64_t)(1 << 20) / std::max<int64_t>(ntuple * nB, 1);
-    }
-    ns = std::max<int64_t>(1, std::min<int64_t>(ns, 1024));
-    int64_t rows = (nrows + ns - 1) / ns;
-    return (int)std::max<int64_t>(64, rows);
+    auto rows_of = [&](int64_t ns, int64_t least) {
+        ns = std::max<int64_t>(1, std::min<int64_t>(ns, 1024));
+        return std::max<int64_t>(least, (nrows + ns - 1) / ns);
+    };
+    const int64_t ns = (int64_t)(1 << 20) / std::max<int64_t>(ntuple * nB, 1);
+    if (!use_couple4(nk, nbins, ntuple, nB)) return (int)rows_of(ns, 64);
+    // one block per (b1, 256 tuples, split): aim at ~1024 blocks per b1
+    const int64_t tblocks = (ntuple + kBlock - 1) / kBlock;
+    const int64_t want = (1024 + tblocks - 1) / std::max<int64_t>(tblocks, 1);
+    if (nbins == kNB4) return (int)rows_of(want, 64);
+    // Bin counts without tiles of primaries: a split's sum and the sum over the splits
+    // round least when both are sqrt(nrows) long, and no more than k_couple's would
+    // up to as many splits as those have rows: the former, or within the latter as many
+    // as make 1024 blocks (FP32 path, 9 bins, lmax 3, 8k primaries: 0.106 ms, k_couple
+    // 0.130), and no more than 64 MiB of partial sums.
+    const int64_t few = std::min(rows_of(ns, 64), 1024 / (tblocks * (nbins - 2)) + 1);
+    const int64_t most = std::min(want, ((int64_t)64 << 20) / (8 * ntuple * nB));
+    return (int)rows_of(std::max(ns, std::min(most, std::max((int64_t)std::sqrt((double)nrows), few))), 32);
 }
 
 __global__ void k_reduce(ReduceArgs a)
@@ -311,7 +317,8 @@ int launch4(const CoupleArgs& a, hipStream_t stream)
 // Several first bins share a launch so that no launch's end leaves the chip idle for
 // long; the register use of a launch is that of its largest, which keeps the largest
 // apart at 10 bins (4PCF lmax 5, 60k primaries, ms: FP64 {8..10} in one launch 3.08, {10}
-// alone 2.96; FP32 2.30, 2.07).
+// alone 2.96; FP32 2.30, 2.07).  Other counts, with one set of sums, take one launch (8
+// bins 1.45, in two launches 1.59; FP32 path, 4k primaries, lmax 3, 9 bins 0.081, 0.104).
 int launch4_tiled(const CoupleArgs& a, hipStream_t stream)   // FP64, 10 bins
 {
     int rc = launch4<double, double, true, kNB4, kNB4>(a, stream);
@@ -321,9 +328,8 @@ int launch4_tiled(const CoupleArgs& a, hipStream_t stream)   // FP64, 10 bins
 template <typename TI>
 int launch4_fp64(const CoupleArgs& a, hipStream_t stream)    // other bin counts
 {
-    if (a.nbins > kNB4) return launch4<TI, double, false, 3, kNB4Max>(a, stream);
-    const int rc = launch4<TI, double, false, 8, kNB4 - 1>(a, stream);
-    return rc != (int)hipSuccess ? rc : launch4<TI, double, false, 3, 7>(a, stream);
+    return a.nbins > kNB4 ? launch4<TI, double, false, 3, kNB4Max>(a, stream)
+                          : launch4<TI, double, false, 3, kNB4 - 1>(a, stream);
 }
 int launch4_fp32(const CoupleArgs& a, hipStream_t stream)
 {
