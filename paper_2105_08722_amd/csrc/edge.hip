@@ -48,7 +48,7 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ matrix build
 // Terms of the entries (L'', 64 consecutive L) as a block [t][lane] padded to the
-// longest of the 64 lists (value 0, L' = 0): a wave reads them with two coalesced
+// longest of the 64 lists (value 0, L' = n: f is 0 there): a wave reads them with two coalesced
 // loads per term.  Read as one list per entry, each lane's loads were 4 bytes and 8
 // bytes of cache lines of its own.
 __global__ void __launch_bounds__(256) k_edge_ell(int n, const int64_t* __restrict__ row_start,
@@ -69,13 +69,13 @@ __global__ void __launch_bounds__(256) k_edge_ell(int n, const int64_t* __restri
         cnt = row_start[(int64_t)L * n + Lpp + 1] - t0;
     }
     for (int64_t t = 0; t < w; ++t) {
-        lp[o + t * kWave + lane] = t < cnt ? (uint16_t)term_lp[t0 + t] : (uint16_t)0;
+        lp[o + t * kWave + lane] = t < cnt ? (uint16_t)term_lp[t0 + t] : (uint16_t)n;
         val[o + t * kWave + lane] = t < cnt ? term_val[t0 + t] : 0.0;
     }
 }
 
 // One workgroup per (group of G bin tuples, range of L''): f of the G bin tuples sits
-// in LDS ([L'][G]); a wave takes 64 entries (L'', 64 L), a lane per L, and adds each
+// in LDS ([L'][G], zeros in row n); a wave takes 64 entries (L'', 64 L), a lane per L, and adds each
 // term to all G sums (6PCF lmax 3, 112M terms above the diagonal times 252 bin tuples:
 // 15.4 ms).  Bound by the LDS reads of f (G values per lane and term, at
 // random L'): the lanes start their G / 2 reads of 16 bytes at different pairs, since
@@ -83,14 +83,14 @@ __global__ void __launch_bounds__(256) k_edge_ell(int n, const int64_t* __restri
 template <int G>
 __global__ void __launch_bounds__(kEdgeThreads) k_edge_matrix(EdgeArgs a, int B_lo, int nB_here, int rows_per_block)
 {
-    extern __shared__ __align__(16) double f[];   // [nlam][G]
+    extern __shared__ __align__(16) double f[];   // [nlam + 1][G]
     constexpr int NC = G / 2;
     const int n = a.nlam;
     const int B0 = B_lo + blockIdx.x * G;
     const int nb = min(G, B_lo + nB_here - B0);
-    for (int i = threadIdx.x; i < n * G; i += kEdgeThreads) {
+    for (int i = threadIdx.x; i < (n + 1) * G; i += kEdgeThreads) {
         const int lp = i / G, g = i - lp * G;
-        f[i] = g < nb ? a.rmult[(size_t)lp * a.nB + B0 + g] / a.rmult[B0 + g] : 0.0;
+        f[i] = lp < n && g < nb ? a.rmult[(size_t)lp * a.nB + B0 + g] / a.rmult[B0 + g] : 0.0;
     }
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -166,7 +166,7 @@ int launch_edge_matrix(const EdgeArgs& a, int B_lo, int nB_here, hipStream_t str
     // ~2048 blocks: the first row ranges hold twice the average work
     const int gy = std::max(1, std::min(a.nlam, (2048 + gx - 1) / gx));
     const int rows = (a.nlam + gy - 1) / gy;
-    const size_t lds = sizeof(double) * (size_t)a.nlam * G;
+    const size_t lds = sizeof(double) * (size_t)(a.nlam + 1) * G;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_edge_matrix<G>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
@@ -769,7 +769,7 @@ int launch_edge(const EdgeArgs& a, int B_lo, int nb, hipStream_t stream)
     if (nb == 0 || a.nlam == 0) return (int)hipSuccess;
     if (a.nlam > kEdgeMaxMultiplets) return (int)hipErrorInvalidValue;
     // eight bin tuples per block while their f tables fit the LDS, else four
-    LUTRY(a.nlam * 8 * sizeof(double) <= 150 * 1024 ? launch_edge_matrix<8>(a, B_lo, nb, stream)
+    LUTRY((a.nlam + 1) * 8 * sizeof(double) <= 150 * 1024 ? launch_edge_matrix<8>(a, B_lo, nb, stream)
                                                     : launch_edge_matrix<4>(a, B_lo, nb, stream));
     LuArgs u;
     u.n = a.nlam;
