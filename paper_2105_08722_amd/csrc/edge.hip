@@ -44,6 +44,7 @@ constexpr int kOuter = 2 * kPanel;  // columns per update of the trailing matrix
 constexpr int kSub = 8;             // columns a panel eliminates in registers
 
 typedef double d2 __attribute__((ext_vector_type(2)));
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // a pair at any column
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ matrix build
@@ -588,7 +589,7 @@ __global__ void __launch_bounds__(256, 2) k_lu_gemm(LuArgs u, int o, int K, int 
             pa[e] = *reinterpret_cast<const d2*>(P + (size_t)(k0 + e * (512 / TM)) * u.mp);
 #pragma unroll
         for (int e = 0; e < NB; ++e)
-            pb[e] = *reinterpret_cast<const d2*>(Ur + (size_t)(k0 + e * (512 / TN)) * u.ld);
+            pb[e] = *reinterpret_cast<const d2u*>(Ur + (size_t)(k0 + e * (512 / TN)) * u.ld);
     };
     fetch(0);
     d4 acc[MT][NT];
