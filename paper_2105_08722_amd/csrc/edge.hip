@@ -447,9 +447,10 @@ __global__ void __launch_bounds__(kEdgeThreads) k_lu_panel(LuArgs u, int o, int 
 #pragma unroll
                 for (int c = 0; c < kSub; ++c)
                     if (c0 + c < kb) {
+                        double p = a[r][0] * U8[c0 + c][0];
 #pragma unroll
-                        for (int k = 0; k < kSub; ++k) v[c] -= a[r][k] * U8[c0 + c][k];
-                        e[(size_t)c * u.mp] = v[c];
+                        for (int k = 1; k < kSub; ++k) p = fma(a[r][k], U8[c0 + c][k], p);
+                        e[(size_t)c * u.mp] = v[c] - p;
                     }
             }
         }
@@ -530,23 +531,38 @@ __global__ void __launch_bounds__(256) k_lu_rows(LuArgs u, int o, int jo, int kb
 #pragma unroll
         for (int t = 0; t < kPanel; ++t) a[t] = t < kb ? A[(size_t)(o + jo + t) * ld] : 0.0;
     }
-    [&]<int... T>(std::integer_sequence<int, T...>) {
+    // eight rows at a time: among themselves one by one, the rows below by their sum
+    [&]<int... G>(std::integer_sequence<int, G...>) {
         ([&] {
-            if (T < kb) {
-                if (SOLVE) {
+            constexpr int T0 = G * kSub;
+            if (SOLVE && T0 < kb) {
 #pragma unroll
-                    for (int i = T + 1; i < kPanel; ++i) a[i] -= Ls[T * kPanel + i] * a[T];
+                for (int t = T0; t < T0 + kSub; ++t)
+#pragma unroll
+                    for (int i = t + 1; i < T0 + kSub; ++i) a[i] -= Ls[t * kPanel + i] * a[t];
+#pragma unroll
+                for (int i = T0 + kSub; i < kPanel; ++i) {
+                    double p = Ls[T0 * kPanel + i] * a[T0];
+#pragma unroll
+                    for (int t = T0 + 1; t < T0 + kSub; ++t) p = fma(Ls[t * kPanel + i], a[t], p);
+                    a[i] -= p;
                 }
-                A[(size_t)(o + jo + T) * ld] = a[T];
             }
+#pragma unroll
+            for (int t = T0; t < T0 + kSub; ++t)
+                if (t < kb) A[(size_t)(o + jo + t) * ld] = a[t];
         }(), ...);
-    }(std::make_integer_sequence<int, kPanel>{});
+    }(std::make_integer_sequence<int, kPanel / kSub>{});
 }
 
 // A[r][c] -= sum_{k < K} P[k][r] A[o + k][c] for rows r0 <= r < r1 and columns
 // c0 <= c < c1: tiles of TM x TN by four waves, the operands of 16 k staged in LDS while
-// the next 16 are on their way to registers, 16 x 16 x 4 FP64 matrix instructions with A
-// itself as the accumulator.  The LDS rows are 16 doubles longer than a multiple of 32,
+// the next 16 are on their way to registers, 16 x 16 x 4 FP64 matrix instructions.  The
+// products are summed by themselves and then subtracted, here and in the steps below 64
+// columns: added to A one by one (with A as the accumulator), each was rounded at
+// the size of A, and systems of 65 to 585 multiplets were solved 1.5 to 10 times less
+// exactly (6PCF lmax 3, 252 systems: 86.0 ms, 84.3 with A as the accumulator, 100 with A
+// read by a wave all at once at the end).  The LDS rows are 16 doubles longer than a multiple of 32,
 // so that the two k rows a half-wave reads lie on different halves of the banks.  Tiles
 // at the edge read L and U past the panel's rows and columns: those products land in
 // rows and columns that are not stored.
@@ -598,13 +614,12 @@ __global__ void __launch_bounds__(256, 2) k_lu_gemm(LuArgs u, int o, int K, int 
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                acc[i][j][q] = (row(i, q) < r1 && col(j) < c1) ? *at(row(i, q), col(j)) : 0.0;
+            for (int q = 0; q < 4; ++q) acc[i][j][q] = 0.0;
     for (int k0 = 0; k0 < K; k0 += kGemmK) {
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < NA; ++e)
-            *reinterpret_cast<d2*>(&As[(ka + e * (512 / TM)) * SA + ra]) = -pa[e];
+            *reinterpret_cast<d2*>(&As[(ka + e * (512 / TM)) * SA + ra]) = pa[e];
 #pragma unroll
         for (int e = 0; e < NB; ++e) *reinterpret_cast<d2*>(&Bs[(kc + e * (512 / TN)) * SB + cc]) = pb[e];
         __syncthreads();
@@ -623,13 +638,25 @@ __global__ void __launch_bounds__(256, 2) k_lu_gemm(LuArgs u, int o, int K, int 
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i], y[j], acc[i][j], 0, 0, 0);
         }
     }
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
+    // A of one row of tiles, on its way while the row before is stored
+    d4 old[2][NT];
+    auto load = [&](int i) {
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (row(i, q) < r1 && col(j) < c1) *at(row(i, q), col(j)) = acc[i][j][q];
+                old[i & 1][j][q] = (row(i, q) < r1 && col(j) < c1) ? *at(row(i, q), col(j)) : 0.0;
+    };
+    load(0);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        if (i + 1 < MT) load(i + 1);
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (row(i, q) < r1 && col(j) < c1) *at(row(i, q), col(j)) = old[i & 1][j][q] - acc[i][j][q];
+    }
 }
 
 // Back substitution on U, 64 unknowns at a time: wave 0 solves their triangle, then
