@@ -42,6 +42,7 @@ constexpr int kEdgeThreads = 1024;
 constexpr int kPanel = 64;          // columns of one panel
 constexpr int kOuter = 2 * kPanel;  // columns per update of the trailing matrix
 constexpr int kSub = 8;             // columns a panel eliminates in registers
+constexpr int kSmall = 32;          // multiplets of a system that one wave solves
 
 typedef double d2 __attribute__((ext_vector_type(2)));
 typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // a pair at any column
@@ -175,6 +176,7 @@ int launch_edge_matrix(const EdgeArgs& a, int B_lo, int nB_here, hipStream_t str
         a, B_lo, nB_here, rows);
     e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
+    if (a.nlam <= kSmall && !a.M_out) return (int)hipSuccess;   // k_edge_small reads above the diagonal alone
     const unsigned nblk = (unsigned)((a.nlam + kWave - 1) / kWave);
     k_edge_mirror<<<dim3(nblk, nblk, (unsigned)nB_here), dim3(256), 0, stream>>>(a.A, a.nlam, a.ld);
     if (a.M_out)
@@ -712,6 +714,62 @@ __global__ void __launch_bounds__(kEdgeThreads) k_lu_back(LuArgs u, const int32_
     if (tid == 0 && bad) atomicAdd(nbad, 1u);
 }
 
+// Systems of up to kSmall multiplets whole, a wave each, matrix and right-hand side in
+// LDS, instead of the steps above, whose 6 launches of a few us were most of a small
+// call (device time, steps above / here / one workgroup per system in global memory:
+// 3PCF lmax 10, 10 bins, 11 multiplets 0.062 / 0.018 / 0.044 ms; 6PCF lmax 1, 16 bins, 26
+// multiplets x 4,368 systems 1.47 / 0.08 / 1.98).  A lane per row up to 32 rows.
+__global__ void __launch_bounds__(kWave) k_edge_small(const double* __restrict__ A0, int n, int ld,
+                                                      const double* __restrict__ nmult,
+                                                      const double* __restrict__ rmult, int B_lo, int nB,
+                                                      const int32_t* __restrict__ keep, int nout,
+                                                      double* __restrict__ zeta, unsigned* __restrict__ nbad)
+{
+    __shared__ double a[kSmall][kSmall + 1];        // column n: the right-hand side
+    __shared__ double xs[kSmall];
+    const int b = blockIdx.x, lane = threadIdx.x, B = B_lo + b;
+    const double* A = A0 + (size_t)b * n * ld;
+    const double r0 = rmult[B];
+    bool bad = !(r0 != 0.0) || !std::isfinite(r0);
+    for (int e = lane; e < n * n; e += kWave) {     // the part above the diagonal, as k_edge_mirror
+        const int i = e / n, c = e - i * n;
+        a[i][c] = A[(size_t)min(i, c) * ld + max(i, c)];
+    }
+    if (lane < n) a[lane][n] = nmult[(size_t)lane * nB + B] / r0;
+    __syncthreads();
+    for (int k = 0; k < n && !bad; ++k) {
+        const bool in = lane >= k && lane < n;
+        const double v = in ? fabs(a[lane][k]) : -1.0;
+        const double wm = wave_max(v);
+        const unsigned long long hit = __builtin_amdgcn_ballot_w64(in && v == wm);
+        const int p = hit ? (int)__builtin_ctzll(hit) : k;
+        const double pv = a[p][k];
+        bad = !hit || !(pv != 0.0) || !std::isfinite(pv);
+        if (bad) break;
+        if (p != k && lane >= k && lane <= n) {
+            const double y = a[k][lane];
+            a[k][lane] = a[p][lane];
+            a[p][lane] = y;
+        }
+        __syncthreads();
+        if (lane > k && lane < n) {
+            const double l = a[lane][k] / pv;
+            for (int c = k + 1; c <= n; ++c) a[lane][c] -= l * a[k][c];
+        }
+        __syncthreads();
+    }
+    double x = lane < n ? a[lane][n] : 0.0;
+    for (int k = n - 1; k >= 0 && !bad; --k) {
+        const double xk = __shfl(x, k) / a[k][k];
+        if (lane == k) x = xk;
+        else if (lane < k) x -= a[lane][k] * xk;
+    }
+    if (lane < n) xs[lane] = x;
+    __syncthreads();
+    for (int i = lane; i < nout; i += kWave) zeta[(size_t)i * nB + B] = bad ? NAN : xs[keep[i]];
+    if (lane == 0 && bad) atomicAdd(nbad, 1u);
+}
+
 template <int TM, int TN>
 int launch_lu_gemm(const LuArgs& u, int o, int K, int r0, int r1, int c0, int c1, hipStream_t s)
 {
@@ -799,6 +857,11 @@ int launch_edge(const EdgeArgs& a, int B_lo, int nb, hipStream_t stream)
     // eight bin tuples per block while their f tables fit the LDS, else four
     LUTRY((a.nlam + 1) * 8 * sizeof(double) <= 150 * 1024 ? launch_edge_matrix<8>(a, B_lo, nb, stream)
                                                     : launch_edge_matrix<4>(a, B_lo, nb, stream));
+    if (a.nlam <= kSmall) {
+        k_edge_small<<<dim3((unsigned)nb), dim3(kWave), 0, stream>>>(a.A, a.nlam, a.ld, a.nmult, a.rmult, B_lo, a.nB,
+                                                                    a.keep, a.nout, a.zeta, a.nbad);
+        return (int)hipGetLastError();
+    }
     LuArgs u;
     u.n = a.nlam;
     u.ld = a.ld;

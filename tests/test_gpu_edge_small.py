@@ -1,0 +1,52 @@
+"""Edge systems that one wave solves (up to 32 multiplets) and the first sizes beyond,
+against numpy's solve of the device's own matrices, windows far from diagonal; systems
+without a solution beside solved ones.  Bound: as for the blocked solve, two
+backward-stable solvers agree to about cond(A) * eps."""
+import numpy as np
+import pytest
+
+from paper_2105_08722_amd import encore
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,lmax,nbins,allp", [(3, 0, 3, False), (4, 1, 4, False), (3, 10, 6, False), (4, 2, 5, True),
+                                               (4, 3, 5, False), (6, 1, 7, False), (4, 3, 4, True), (6, 1, 7, True)])
+def test_small_systems(N, lmax, nbins, allp):
+    n, nB = encore.num_multiplets(N, lmax, allp), encore.num_bin_tuples(N, nbins)
+    print("[edge-small] N %d lmax %d n %d" % (N, lmax, n), flush=True)
+    rng = np.random.default_rng(n)
+    R = rng.normal(0.0, 1.0, (n, nB))
+    R[0] = rng.uniform(1.0, 3.0, nB)
+    Nm = rng.normal(0.0, 1.0, (n, nB))
+    with encore.Context(0) as ctx:
+        z, M, bad = encore.edge_correct(ctx, N, lmax, nbins, Nm, R, allparity=allp, return_coupling=True)
+        zc = encore.edge_correct(ctx, N, lmax, nbins, Nm, R, allparity=allp)
+        assert bad == 0 and np.array_equal(z, zc)
+        for b in range(nB):
+            assert np.array_equal(M[b], M[b].T)
+            zr = np.linalg.solve(M[b].T, Nm[:, b] / R[0, b])
+            assert np.max(np.abs(z[:, b] - zr)) <= 1e-13 * np.linalg.cond(M[b]) * np.max(np.abs(zr))
+        R[0, 0], R[0, 1], R[0, 2] = 0.0, np.inf, np.nan
+        if n > 1:
+            R[1, nB - 1] = np.inf
+        z2, _, bad = encore.edge_correct(ctx, N, lmax, nbins, Nm, R, allparity=allp, return_coupling=True)
+        none = sorted({0, 1, 2} | ({nB - 1} if n > 1 else set()))
+        assert bad == len(none)
+        assert np.all(np.isnan(z2[:, none]))
+        assert np.array_equal(np.delete(z2, none, axis=1), np.delete(z, none, axis=1))
+
+
+def test_singular_matrix():
+    """M = c [[1, f], [f, 1]] with f = 1: the second pivot is exactly zero."""
+    n, nB = encore.num_multiplets(3, 1), encore.num_bin_tuples(3, 4)
+    assert n == 2
+    rng = np.random.default_rng(3)
+    R = np.vstack([np.full(nB, 2.0), rng.uniform(-1.0, 1.0, nB)])
+    Nm = rng.normal(size=(n, nB))
+    R[1, 3] = R[0, 3]
+    with encore.Context(0) as ctx:
+        z, M, bad = encore.edge_correct(ctx, 3, 1, 4, Nm, R, return_coupling=True)
+    assert np.all(np.abs(M[3]) == M[3, 0, 0]) and M[3, 0, 1] == M[3, 1, 0]
+    assert bad == 1 and np.all(np.isnan(z[:, 3]))
+    assert np.all(np.isfinite(z[:, :3])) and np.all(np.isfinite(z[:, 4:]))
