@@ -35,18 +35,3 @@ def test_small_systems(N, lmax, nbins, allp):
         assert bad == len(none)
         assert np.all(np.isnan(z2[:, none]))
         assert np.array_equal(np.delete(z2, none, axis=1), np.delete(z, none, axis=1))
-
-
-def test_singular_matrix():
-    """M = c [[1, f], [f, 1]] with f = 1: the second pivot is exactly zero."""
-    n, nB = encore.num_multiplets(3, 1), encore.num_bin_tuples(3, 4)
-    assert n == 2
-    rng = np.random.default_rng(3)
-    R = np.vstack([np.full(nB, 2.0), rng.uniform(-1.0, 1.0, nB)])
-    Nm = rng.normal(size=(n, nB))
-    R[1, 3] = R[0, 3]
-    with encore.Context(0) as ctx:
-        z, M, bad = encore.edge_correct(ctx, 3, 1, 4, Nm, R, return_coupling=True)
-    assert np.all(np.abs(M[3]) == M[3, 0, 0]) and M[3, 0, 1] == M[3, 1, 0]
-    assert bad == 1 and np.all(np.isnan(z[:, 3]))
-    assert np.all(np.isfinite(z[:, :3])) and np.all(np.isfinite(z[:, 4:]))
