@@ -11,8 +11,8 @@
 //   B[(i, c)][col] = (Re, Im)(w_i a~^{b_K}_{l_K mu}(i)),
 //
 // so that sum_K A B = sum_i w_i Q[P a~].  Rows and columns are grouped in blocks
-// of fixed (mu, parity of l_K, beta = b_{K-1}); a block's columns are the bins b_K > beta, so
-// every computed entry has strictly increasing bins.  The blocks are cut into
+// of fixed (mu, beta = b_{K-1}) and, in most plans, parity of l_K; a block's columns are
+// the bins b_K > beta, so every computed entry has strictly increasing bins.  The blocks are cut into
 // 16 x 16 output tiles; one wave owns up to four tiles of one block (a "wave
 // job") and forms each of its row operands once per primary.
 #include "mfma_plan.h"
@@ -61,31 +61,75 @@ int build_mfma_plan(int N, int lmax, bool allparity, int nbins, MfmaPlan& P)
     P = MfmaPlan();
     P.K = K; P.KF = KF; P.nlm = nlm; P.nbins = nbins; P.nent = nbins * nlm;
 
-    // row keys (rho, q) and column ells per (mu, parity of l_K): a row meets only
-    // columns of one parity (that of its own l sum, or for the Im rows of odd
-    // multiplets the other; 4PCF lmax 5 over 800k primaries 14.3 -> 12.8 ms: 2029
-    // operand tiles formed per K block instead of 2346, 1660 output tiles instead of
-    // 2008).  The 3PCF's few rows (one l each) fill their tiles better together: 501
-    // operand tiles at lmax 10 instead of 875.
+    // Row keys (rho, q) and column ells per class: mu and, by_parity, the parity of l_K.  A
+    // row meets only columns of one parity (that of its own l sum, or for the Im rows of
+    // odd multiplets the other), so classes by parity halve the output tiles of a row
+    // tile: 4PCF lmax 5 over 800k primaries 14.3 -> 12.8 ms, 1660 output tiles instead
+    // of 2008.  Where a block's columns fill no more than a tile or two anyway, they only
+    // add row tiles to pad: 4PCF lmax 3, 6 bins, 30k primaries 0.083 ms in one class per
+    // mu, 0.111 by parity; lmax 2, 6 bins, 250k 0.44, 0.60.  The choice is by the number of
+    // wave jobs, with 6 jobs for a launch (a shape in use): of 129 plans up to lmax 4 none is
+    // then more than 6% slower than in one class per mu, at 3k, 30k or 250k primaries.
+    // The 3PCF's few rows (one l each) fill their tiles better together: 501 operand
+    // tiles at lmax 10 instead of 875.
     using Cls = std::pair<int, int>;
+    bool by_parity = N != 3;
     auto cls = [&](int64_t t) {
-        return Cls(tt.tuple_m[t * K + K - 1], N == 3 ? 0 : tt.tuple_l[t * K + K - 1] & 1);
+        return Cls(tt.tuple_m[t * K + K - 1], by_parity ? tt.tuple_l[t * K + K - 1] & 1 : 0);
     };
     std::map<Cls, std::map<std::vector<int>, int>> rowkeys;   // class -> key -> index
     std::map<Cls, std::map<int, int>> colells;                // class -> l_K -> index
-    for (int64_t t = 0; t < tt.ntuple; ++t) {
-        const Cls mu = cls(t);
-        std::vector<int> key;
-        for (int k = 0; k < KF; ++k) {
-            key.push_back(tt.tuple_l[t * K + k]);
-            key.push_back(tt.tuple_m[t * K + k]);
+    auto collect = [&]() {
+        rowkeys.clear();
+        colells.clear();
+        for (int64_t t = 0; t < tt.ntuple; ++t) {
+            const Cls mu = cls(t);
+            std::vector<int> key;
+            for (int k = 0; k < KF; ++k) {
+                key.push_back(tt.tuple_l[t * K + k]);
+                key.push_back(tt.tuple_m[t * K + k]);
+            }
+            key.push_back(tt.tuple_odd[t]);
+            auto& rk = rowkeys[mu];
+            if (!rk.count(key)) { const int id = (int)rk.size(); rk[key] = id; }
+            auto& ce = colells[mu];
+            const int lK = tt.tuple_l[t * K + K - 1];
+            if (!ce.count(lK)) { const int id = (int)ce.size(); ce[lK] = id; }
         }
-        key.push_back(tt.tuple_odd[t]);
-        auto& rk = rowkeys[mu];
-        if (!rk.count(key)) { const int id = (int)rk.size(); rk[key] = id; }
-        auto& ce = colells[mu];
-        const int lK = tt.tuple_l[t * K + K - 1];
-        if (!ce.count(lK)) { const int id = (int)ce.size(); ce[lK] = id; }
+    };
+    // wave jobs, and 6 per shape in use, of blocks with these numbers of keys and ells
+    auto cost = [&](const std::vector<std::pair<int64_t, int64_t>>& classes) {
+        int64_t jobs = 0;
+        bool used[kNumMfmaShapes] = {};
+        for (const auto& c : classes)
+            for (int beta = K - 2; beta <= nbins - 2; ++beta) {
+                const int64_t nrt = (c.first * (int64_t)binomial(beta, K - 2) + 15) / 16;
+                int64_t nct = (c.second * (nbins - 1 - beta) + 15) / 16;
+                for (; nrt > 0 && nct > 0; nct -= 4) {
+                    const int shape = (int)std::min<int64_t>(nct, 4) - 1;
+                    jobs += (nrt + kMfmaShapes[shape].RT - 1) / kMfmaShapes[shape].RT;
+                    used[shape] = true;
+                }
+            }
+        for (bool u : used) jobs += u ? 6 : 0;
+        return jobs;
+    };
+    collect();
+    if (by_parity) {
+        std::vector<std::pair<int64_t, int64_t>> split, whole;
+        int last = -1;
+        for (const auto& kv : rowkeys) {   // by mu, then parity; the parities share no key and no ell
+            const int64_t nk = (int64_t)kv.second.size(), ne = (int64_t)colells[kv.first].size();
+            split.push_back({nk, ne});
+            if (kv.first.first != last) whole.push_back({0, 0});
+            last = kv.first.first;
+            whole.back().first += nk;
+            whole.back().second += ne;
+        }
+        if (cost(whole) <= cost(split)) {
+            by_parity = false;
+            collect();
+        }
     }
     // index of a prefix bin tuple (b_1 .. b_{K-2}) among those below beta
     struct BlockInfo {
