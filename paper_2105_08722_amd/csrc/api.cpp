@@ -168,11 +168,15 @@ int run_jobs(encore_ctx* ctx, Exec& x, const DevTables* tb, int64_t cap, const s
     size_t jcur = 0;
     int64_t jpos = 0;   // rows of jobs[jcur] already done
     std::vector<Chunk> chunks;
+    NpcfPlan spl = pl;   // of a slice, whose jobs have the same bins per item
     while (jcur < jobs.size()) {
         chunks.clear();
         int64_t rows = 0;
         while (jcur < jobs.size() && rows < cap && chunks.size() < 4096) {
             const JobRows& J = jobs[jcur];
+            const int nbg = J.nbg < 0 ? pl.nbg : J.nbg;
+            if (chunks.empty()) spl.nbg = nbg;
+            else if (nbg != spl.nbg && J.nprim > jpos) break;        // next slice
             const int64_t sr = srows[jcur];
             int64_t take = J.nprim - jpos;
             if (take > cap - rows) take = (cap - rows) / sr * sr;   // whole splits only
@@ -190,7 +194,7 @@ int run_jobs(encore_ctx* ctx, Exec& x, const DevTables* tb, int64_t cap, const s
                 return fail(ENCORE_EINVAL, "slice row cap below the coupling split length");
             break;
         }
-        if ((rc = run_slice(x, pl, tb, edges, chunks, &t_gather, &t_couple))) return rc;
+        if ((rc = run_slice(x, spl, tb, edges, chunks, &t_gather, &t_couple))) return rc;
         ++nslice;
     }
     std::vector<double> sc;
@@ -414,6 +418,7 @@ int encore_npcf(encore_ctx* ctx, const encore_grid* grid, int npcf, int lmax, in
         int rc2;
         if ((rc2 = make_primaries(x, grid, primary_subset, n_subset, &nprim))) return rc2;
         std::vector<JobRows> jobs{JobRows{grid, (const int32_t*)x.prim.p, nprim}};
+        if (primary_subset) jobs[0].nbg = subset_nbg(ctx, pl, grid->g);
         return run_jobs(ctx, jobs, pl, flags, edges, volume, zeta);
     });
 }
@@ -457,6 +462,7 @@ int encore_npcf_batch(encore_ctx* ctx, const encore_grid* const* grids, int njob
             if ((rc2 = fill_primaries(x, grids[j], subset_of(j), subset_of(j) ? n_subsets[j] : 0, dst, &np)))
                 return rc2;
             jobs[j] = JobRows{grids[j], dst, np};
+            if (subset_of(j)) jobs[j].nbg = subset_nbg(ctx, pl, grids[j]->g);
             off += np;
         }
         return run_jobs(ctx, jobs, pl, flags, edges, 0.0, zeta);
@@ -877,7 +883,8 @@ int encore_debug_alm(encore_ctx* ctx, const encore_grid* grid, int lmax, int nbi
     ga.nrows = (int)nlaunch;
     NpcfPlan gpl;
     gpl.lmax = lmax; gpl.prec = cprec; gpl.nbins = nbins;
-    const int nbg = ctx_nbg(ctx, gpl);   // the configuration encore_npcf launches
+    // the configuration encore_npcf launches over every point, or over these primaries
+    const int nbg = full ? ctx_nbg(ctx, gpl) : subset_nbg(ctx, gpl, g);
     if (e == hipSuccess) e = (hipError_t)launch_gather(ga, lmax, prec, nbg, 0, s);
     if (e == hipSuccess)
         e = (hipError_t)launch_to_double(x.alm.p, prec == 0 ? 0 : 1, nlaunch * per, (double*)x.zeta.p, s);

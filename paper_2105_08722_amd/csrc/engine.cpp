@@ -660,6 +660,12 @@ int ctx_nbg(encore_ctx* ctx, const NpcfPlan& pl)
     return it == ctx->tuned_nbg.end() ? 0 : it->second;
 }
 
+int subset_nbg(encore_ctx* ctx, const NpcfPlan& pl, const DevGrid& g)
+{
+    const int wide = gather_wide_bins(pl.lmax, gather_precision(pl.prec), g.n);
+    return wide ? wide : ctx_nbg(ctx, pl);
+}
+
 void ctx_cells(encore_ctx* ctx, double* div, double* xsub)
 {
     std::lock_guard<std::mutex> lock(ctx->tab_mu);

@@ -254,6 +254,7 @@ struct JobRows {
     int64_t nprim;
     const double4* Pq = nullptr;   // random-split jobs (see Chunk)
     const void* cache = nullptr;
+    int nbg = -1;                  // gather bins per work item (-1: the plan's)
 };
 
 // The hot path over several jobs on exec x with tables tb (the caller holds
@@ -265,6 +266,8 @@ int run_jobs(encore_ctx* ctx, Exec& x, const DevTables* tb, int64_t cap, const s
 
 // tuned bins per work item for a call (0: default); thread-safe
 int ctx_nbg(encore_ctx* ctx, const NpcfPlan& pl);
+// the same for a job over grid g whose primaries are a subset, in the caller's order
+int subset_nbg(encore_ctx* ctx, const NpcfPlan& pl, const DevGrid& g);
 // destroy the context's gridded-data transform plans
 void mesh_release(encore_ctx* ctx);
 void ctx_cells(encore_ctx* ctx, double* div, double* xsub);

@@ -965,14 +965,15 @@ KernelCfg cfg2()
 
 // Bins per work item: more bins per item mean fewer passes over the candidates and
 // fewer row set-ups, but more accumulator registers and LDS stacks, hence fewer
-// resident waves, and one more compare, rank and select per candidate.  Two bins are
-// best or within 3% of best wherever their accumulators fit (4PCF gather, 200k
-// points at the benchmark density / 50k primaries of the survey wedge, ms: lmax 3
-// FP32 2 bins 12.4 / 5.8, 3 bins 13.4 / 6.8, 4 bins 12.7 / 6.5; lmax 4 FP32 2 bins
-// 12.3 / 6.2, 3 bins 14.6 / 7.3; FP64 at lmax 3 twice the time with 5 bins, at lmax 4 a
-// third more with 3 and 15% more with 1); at lmax 0 and 1 four bins win without clustering (11.3 against
-// 12.2) and lose on the wedge (5.8 against 5.1), so both are compiled and
-// encore_autotune picks one per job shape (ENCORE_GATHER_NBG overrides).
+// resident waves, and one more compare, rank and select per candidate.  Where the
+// primaries come in cell order, two bins are best or within 3% of best wherever their
+// accumulators fit (gather, 200k points at the benchmark density / every point of a 200k
+// wedge, 10 bins, FP32, ms: lmax 2 2 bins 9.0 / 13.7, 4 bins 11.2 / 17.3, 6 bins 13.3 / 21.7;
+// lmax 3 2 bins 9.6 / 14.7, 3 bins 11.3 / 16.9, 5 bins 11.6 / 18.9; FP64 at lmax 3 twice the
+// time with 5 bins, at lmax 4 a third more with 3 and 15% more with 1).  Primaries in any
+// order read their candidates from the last-level cache once the catalog exceeds the
+// L2s, once per group: the wide variants below (gather_wide_bins), which
+// encore_autotune tries too (ENCORE_GATHER_NBG overrides both).
 int nbg_env()
 {
     static int v = [] {
@@ -1006,9 +1007,9 @@ KernelCfg config(int lmax, int precision, int nbg)
         switch (lmax) {
         case 0: return nbg == 4 ? cfg1<float, 0, 4>() : cfg1<float, 0, 2>();
         case 1: return nbg == 4 ? cfg1<float, 1, 4>() : cfg1<float, 1, 2>();
-        case 2: return cfg1<float, 2, 2>();
-        case 3: return cfg1<float, 3, 2>();
-        case 4: return cfg1<float, 4, 2>();
+        case 2: return nbg == 6 ? cfg1<float, 2, 6>() : cfg1<float, 2, 2>();
+        case 3: return nbg == 5 ? cfg1<float, 3, 5>() : cfg1<float, 3, 2>();
+        case 4: return nbg == 3 ? cfg1<float, 4, 3>() : cfg1<float, 4, 2>();
         case 5: return cfg1<float, 5, 2>();
         case 6: return cfg1<float, 6, 2>();
         case 7: return cfg1<float, 7, 1>();
@@ -1040,11 +1041,22 @@ int gather_group_bins(int lmax, int precision, int nbg) { return config(lmax, pr
 
 std::vector<int> gather_nbg_options(int lmax, int precision)
 {
-    static const std::vector<int> f32[11] = {{2, 4}, {2, 4}, {2}, {2}, {2}, {2}, {2}, {1}, {1}, {1}, {1}};
+    static const std::vector<int> f32[11] = {{2, 4}, {2, 4}, {2, 6}, {2, 5}, {2, 3}, {2}, {2}, {1}, {1}, {1}, {1}};
     static const std::vector<int> f64[11] = {{2}, {2}, {2}, {2}, {2}, {2}, {1}, {1}, {1}, {1}, {1}};
     static const std::vector<int> f32c[11] = {{2, 4}, {2, 4}, {2}, {2}, {2}, {2, 1}, {1}, {1}, {1}, {1}, {1}};
     if (lmax < 0 || lmax > 10) return {};
     return precision == 1 ? f32[lmax] : (precision == 2 ? f32c[lmax] : f64[lmax]);
+}
+
+// The wide variant, for primaries in any order: 200k random primaries of 2M wedge points,
+// 10 bins, FP32, 2 bins per item / wide: lmax 2 69.5 / 49.7 ms, lmax 3 69.5 / 47.7.  From
+// 300k points on it is the faster one at every lmax that has one (300k wedge points lmax 2
+// 0.97 of the time, lmax 3 0.85, lmax 4 0.97; 400k 0.83, 0.75, 0.98), at 250k up to 14% slower,
+// at 100k up to half.  The FP64 accumulators of the other paths have no registers for one.
+int gather_wide_bins(int lmax, int precision, int64_t npoints)
+{
+    if (precision != 1 || npoints < 300000 || lmax > 4) return 0;
+    return gather_nbg_options(lmax, precision).back();
 }
 
 void gather_tables(int lmax, double* kappa)

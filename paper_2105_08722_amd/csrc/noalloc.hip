@@ -167,5 +167,6 @@ extern "C" int encore_npcf_noalloc(encore_ctx* ctx, const encore_grid* grid, int
         (rc = ensure(x.almb, (size_t)((sn.rows + kBlkRows - 1) / kBlkRows) * blk_bytes(tb.mf_nent) + 1024)))
         return rc;
     std::vector<JobRows> jobs{JobRows{grid, (const int32_t*)x.prim.p, np}};
+    if (primary_subset) jobs[0].nbg = subset_nbg(ctx, pl, grid->g);
     return run_jobs(ctx, x, &tb, cap, jobs, pl, flags, edges, volume, zeta);
 }
