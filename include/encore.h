@@ -275,14 +275,16 @@ int encore_mfma_plan_stats(int npcf, int lmax, int nbins, uint32_t flags, int64_
  * (8, 4), (5, 24), (4, 16)) and times,
  * for each, the gather + coupling of this job (as encore_npcf) over a sample of
  * n_sample primaries (16 runs of consecutive cell-sorted primaries spread over the
- * grid, so that neighbouring work items share cells as in a full pass), for every compiled
+ * grid, so that neighbouring work items share cells as in a full pass; with the gather's
+ * grid of a pass over every point, persistent or one wave per item), for every compiled
  * bins-per-work-item value of the gather.  The fastest (d, s) becomes the cell
  * shape of later grids built on ctx; the fastest bins-per-item value is used by
  * later calls with the same lmax, gather precision and nbins.  The default shape
  * and bins per item are kept unless the fastest is more than 2% faster on the
  * sample (sample timings of nearby shapes differ by about that much).  The choice changes
  * only the order of floating-point operations, never what is computed.
- *  report  NULL or [5]: d, s, bins per item, best ms, ms of the default shape.
+ *  report  NULL or [5]: d, s, bins per item, best ms, ms of the default shape; with
+ *          report_len > 5 also 1 if the gathers took the persistent grid, else 0.
  * Errors: as encore_build_grid and encore_npcf; ESIZE if report_len < 5.
  */
 int encore_autotune(encore_ctx* ctx, const double* pos, const double* w, int64_t n, int64_t n_data,

@@ -758,6 +758,8 @@ int encore_autotune(encore_ctx* ctx, const double* pos, const double* w, int64_t
         if (rc == ENCORE_OK) {
             for (size_t q = 0; q < nbgs.size() && rc == ENCORE_OK; ++q) {
                 pl.nbg = nbgs[q];
+                // the kernel that a pass over every point launches, not the sample's few items
+                pl.grid = gather_grid(lmax, gprec, pl.nbg, nbins, std::min(n, cap_rows(pl)));
                 double t = 1e300;
                 for (int rep = 0; rep < 3 && rc == ENCORE_OK; ++rep) {
                     std::vector<JobRows> jobs{JobRows{&tg, (const int32_t*)x.prim.p, np}};
@@ -791,6 +793,7 @@ int encore_autotune(encore_ctx* ctx, const double* pos, const double* w, int64_t
         ctx->tuned_nbg[std::make_tuple(lmax, gprec, nbins)] = best_nbg;
     }
     if (report) {
+        if (report_len > 5) report[5] = gather_grid(lmax, gprec, best_nbg, nbins, std::min(n, cap_rows(pl)));
         report[0] = best_div;
         report[1] = best_xsub;
         report[2] = best_nbg;

@@ -142,6 +142,8 @@ int launch_add_cached(void* alm, int precision, int row0, int nrows, const int32
 int gather_group_bins(int lmax, int precision, int nbg);
 // compiled bins-per-item values for (lmax, precision), the default first
 std::vector<int> gather_nbg_options(int lmax, int precision);
+// the grid of a launch over nrows primaries: 1 persistent, 0 one wave per work item
+int gather_grid(int lmax, int precision, int nbg, int nbins, int64_t nrows);
 // bins per item for primaries in any order over npoints points (0: the default)
 int gather_wide_bins(int lmax, int precision, int64_t npoints);
 void gather_tables(int lmax, double* kappa);

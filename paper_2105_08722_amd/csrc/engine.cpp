@@ -481,6 +481,7 @@ int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl
     HIPTRY(hipMemcpyAsync(splits.p, hsplit.data(), sizeof(int32_t) * hsplit.size(), hipMemcpyHostToDevice, s));
     HIPTRY(hipMemcpyAsync(redp.p, rdst.data(), sizeof(double*) * rdst.size(), hipMemcpyHostToDevice, s));
     const int32_t* dsp = (const int32_t*)splits.p;
+    L.grid = pl.grid;
     // ENCORE_GATHER_PERSISTENT forces the gather's grid (0: static, 1: persistent)
     if (const char* e = getenv("ENCORE_GATHER_PERSISTENT")) L.grid = atoi(e) != 0;
 

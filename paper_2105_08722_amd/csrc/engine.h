@@ -115,6 +115,7 @@ int check_grid_edges(const DevGrid& g, const double* edges, int nbins);
 struct NpcfPlan {
     int N = 0, lmax = 0, nbins = 0, prec = 0;
     int nbg = 0;   // gather bins per work item (0: the compiled default)
+    int grid = -1; // of the gather (launch_gather)
     bool allparity = false;
     int64_t nlam = 0, nB = 0;
 };

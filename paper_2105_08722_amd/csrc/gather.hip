@@ -1085,6 +1085,12 @@ void gather_tables(int lmax, double* kappa)
 // 50,000: 365 -> 381 us).
 constexpr int64_t kPersistentItems = 1 << 18;
 
+int gather_grid(int lmax, int precision, int nbg, int nbins, int64_t nrows)
+{
+    const KernelCfg c = config(lmax, precision, nbg);
+    return c.fnp[0] && nrows * ((nbins + c.nbg - 1) / c.nbg) >= kPersistentItems ? 1 : 0;
+}
+
 namespace {
 
 // Resident workgroups of a persistent kernel on the current device.
@@ -1120,8 +1126,8 @@ int launch_gather(const GatherArgs& a0, int lmax, int precision, int nbg, int gr
     a.ngroups = (a.nbins + c.nbg - 1) / c.nbg;
     const int64_t quads = ((int64_t)a.nrows + kWavesPerBlock - 1) / kWavesPerBlock * a.ngroups;
     if (quads == 0) return (int)hipSuccess;
-    const bool persistent = c.fnp[0] && a.queues &&
-                            (grid == 1 || (grid < 0 && quads * kWavesPerBlock >= kPersistentItems));
+    if (grid < 0) grid = gather_grid(lmax, precision, nbg, a.nbins, a.nrows);
+    const bool persistent = c.fnp[0] && a.queues && grid == 1;
     if (!persistent) a.queues = nullptr;
     for (int g = 0; g < c.nm; ++g) {
         const void* fn = persistent ? c.fnp[g] : c.fn[g];

@@ -311,12 +311,12 @@ def autotune(ctx, pos, w, N, lmax, edges, box=None, n_data=None, precision="fp32
     edges = _f64(edges, (-1,))
     flags = (PRECISIONS[precision] | (PERIODIC if box is not None else 0) |
              (DMR if n_data is not None else 0))
-    rep = np.zeros(5)
+    rep = np.zeros(6)
     _check(lib().encore_autotune(ctx.handle, _ptr(pos), _ptr(w), len(w), int(n_data or 0), _ptr(_box3(box)),
                                  int(N), int(lmax), len(edges) - 1, _ptr(edges), flags, int(n_sample),
-                                 _ptr(rep), 5))
+                                 _ptr(rep), 6))
     return {"cell_divisor": rep[0], "x_subdivision": rep[1], "bins_per_item": int(rep[2]),
-            "best_ms": rep[3], "default_ms": rep[4]}
+            "best_ms": rep[3], "default_ms": rep[4], "persistent": bool(rep[5])}
 
 
 class Plan:
