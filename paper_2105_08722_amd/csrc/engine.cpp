@@ -410,7 +410,7 @@ int64_t job_split_rows(const NpcfPlan& pl, const DevTables* tb, int64_t nprim, i
 }
 
 int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl, const DevTables* tb,
-                  const double* edges, const std::vector<Chunk>& chunks, SliceLaunch& L)
+                  const double* edges, const std::vector<Chunk>& chunks, SliceLaunch& L, bool to_blocked)
 {
     const hipStream_t s = x.s;
     const int nlm = (pl.lmax + 1) * (pl.lmax + 2) / 2;
@@ -459,13 +459,14 @@ int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl
     if (rows > INT32_MAX || hsegs.size() > 65535) return fail(ENCORE_ESIZE, "slice too large");
     const int nsplit = (int)slo.size(), nred = (int)rlo.size();
     int rc;
-    if ((rc = ensure(x.alm, alm_row_bytes(pl) * (size_t)rows))) return rc;
+    const bool rowed = !(blocked && to_blocked);
+    if (rowed && (rc = ensure(x.alm, alm_row_bytes(pl) * (size_t)rows))) return rc;
     // the MFMA coupling reads a blocked copy: whole 16-row blocks, plus 1 KiB that
     // its 1 KiB copy units may read past the last block
     const int ent_blk = blk_entries(tb->mf_nent);
     const int64_t nblk = (rows + kBlkRows - 1) / kBlkRows;
     if (blocked && (rc = ensure(x.almb, (size_t)nblk * blk_bytes(tb->mf_nent) + 1024))) return rc;
-    if ((rc = ensure(x.wprim, sizeof(double) * (size_t)rows))) return rc;
+    if (rowed && (rc = ensure(x.wprim, sizeof(double) * (size_t)rows))) return rc;
     if ((rc = ensure(x.T, sizeof(double) * (size_t)nsplit * (size_t)outs))) return rc;
     if ((rc = ensure(segs, sizeof(GatherSeg) * hsegs.size()))) return rc;
     if ((rc = ensure(splits, sizeof(int32_t) * (size_t)(2 * nsplit + 2 * nred)))) return rc;

@@ -176,8 +176,9 @@ struct SliceLaunch {
     MfmaArgs ma;
     ReduceArgs ra;
 };
+// to_blocked: the caller writes the split-BF16 coupling's blocked copy itself, without rows
 int prepare_slice(Exec& x, Buf& segs, Buf& splits, Buf& redp, const NpcfPlan& pl, const DevTables* tb,
-                  const double* edges, const std::vector<Chunk>& chunks, SliceLaunch& L);
+                  const double* edges, const std::vector<Chunk>& chunks, SliceLaunch& L, bool to_blocked = false);
 int launch_slice_gather(const SliceLaunch& L, const NpcfPlan& pl, hipStream_t s);
 // blocked: the split-BF16 coupling's blocked copy is there already
 int launch_slice_couple(const SliceLaunch& L, const NpcfPlan& pl, const DevTables* tb, hipStream_t s,

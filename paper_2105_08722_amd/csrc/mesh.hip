@@ -320,7 +320,7 @@ extern "C" int encore_npcf_mesh(encore_ctx* ctx, const double* delta, int nmesh,
                 }
                 if (l & 1) (lm < 64 ? odd_lo : odd_hi) |= (uint64_t)1 << (lm & 63);
             }
-        // batched transforms over the nf interleaved fields (element stride nf)
+        // batched transforms over the nf fields, each contiguous;
         // the plans (and their work areas) of the last (nmesh, nf) are kept
         if (!(ctx->mesh_plan && ctx->mesh_plan1 && ctx->mesh_plan_n == nmesh && ctx->mesh_plan_nf == nf)) {
             mesh_release(ctx);
@@ -371,7 +371,7 @@ extern "C" int encore_npcf_mesh(encore_ctx* ctx, const double* delta, int nmesh,
             int64_t take = std::min<int64_t>(ncell - r0, std::max<int64_t>(cap / sr, 1) * sr);
             std::vector<Chunk> chunks{Chunk{&cells, (const int32_t*)x.prim.p, r0, r0 + take, sr, (double*)x.Tjob.p}};
             SliceLaunch L;
-            rc = prepare_slice(x, x.segs, x.splits, x.redp, pl, tb, edges, chunks, L);
+            rc = prepare_slice(x, x.segs, x.splits, x.redp, pl, tb, edges, chunks, L, true);
             if (rc) break;
             hipError_t e = hipEventRecord(x.ev[2], s);
             if (e == hipSuccess) {
