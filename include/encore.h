@@ -416,12 +416,13 @@ int encore_debug_alm(encore_ctx* ctx, const encore_grid* grid, int lmax, int nbi
  *  coupling      NULL or host FP64 [nB][nlam][nlam]: M[B][L][L''].
  *  n_singular    NULL or the number of B without a solution.
  * Device memory: the matrices of nlam^2 FP64 values, at most 32 GiB of them at a time
- * (all nB again when coupling is requested), about 3% more for the panels, the Gaunt
+ * (all nB again when coupling is requested), (nlam + 128) KiB for each one's panels (6%
+ * of the matrices at 2,212 multiplets, 27% at 585), the Gaunt
  * table (first as it is uploaded, in the matrices' place) and the multiplets, in
  * grow-only workspaces kept by the context for later calls; the table is uploaded once
  * per (npcf, lmax, parity).
  * Errors: EINVAL, ESIZE (a buffer too small; the message gives the size),
- * EUNSUPPORTED (more than 4096 multiplets, e.g. npcf = 6 at lmax 4), ENOMEM, EDEVICE.
+ * EUNSUPPORTED (more than 3072 multiplets, e.g. npcf = 6 at lmax 4), ENOMEM, EDEVICE.
  */
 int encore_edge_correct(encore_ctx* ctx, int npcf, int lmax, int nbins, uint32_t flags,
                         const double* nmult, const double* rmult, size_t mult_len, int lmax_out,

@@ -203,9 +203,10 @@ int launch_couple_gemm(const MfmaArgs& a, int KL, int KR, hipStream_t stream);
 // Edge correction: builds the coupling matrices of bin tuples [B_lo, B_lo + nb) from
 // the Gaunt terms and the random multiplets and solves for zeta (NaN for B with R_0 =
 // 0 or a singular matrix, counted in *nbad).
-// Largest multiplet count of the edge-correction solve (four rows per thread of its
-// panels, 16-bit L' in the term lists).
-constexpr int kEdgeMaxMultiplets = 4096;
+// Largest multiplet count of the edge-correction solve (three rows per thread of its
+// panels, 16-bit L' in the term lists).  The counts jump from 2,666 (5PCF lmax 5, all
+// parities) to 4,269 (6PCF lmax 3, all parities).
+constexpr int kEdgeMaxMultiplets = 3072;
 struct EdgeArgs {
     int nlam, nB, nout, ld;     // ld: row stride of A, edge_ld(nlam)
     const double* nmult;        // [nlam][nB] data-minus-random multiplets

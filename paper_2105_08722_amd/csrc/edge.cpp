@@ -80,7 +80,7 @@ extern "C" int encore_edge_correct(encore_ctx* ctx, int npcf, int lmax, int nbin
     a.ld = edge_ld(n);
     int rc;
     // The systems are solved together, as many at once as fit 32 GiB (all of them at
-    // the sizes of the paper's analyses; at 4096 multiplets 251, about one per CU).
+    // the sizes of the paper's analyses; 873 at 2,212 multiplets, 602 at 2,666).
     const int64_t per_b = (int64_t)edge_matrix_bytes(n, 2) - (int64_t)edge_matrix_bytes(n, 1);
     const int64_t chunk = std::min<int64_t>(nB, std::max<int64_t>(1, ((int64_t)32 << 30) / per_b));
     // Workspaces: the context's grow-only buffers, kept for later calls; the Gaunt

@@ -787,7 +787,7 @@ int launch_lu_panel(const LuArgs& u, int o, int jo, int kb, hipStream_t s)
     if (rows <= kEdgeThreads) k_lu_panel<1><<<g, t, 0, s>>>(u, o, jo, kb);
     else if (rows <= 2 * kEdgeThreads) k_lu_panel<2><<<g, t, 0, s>>>(u, o, jo, kb);
     else if (rows <= 3 * kEdgeThreads) k_lu_panel<3><<<g, t, 0, s>>>(u, o, jo, kb);
-    else k_lu_panel<4><<<g, t, 0, s>>>(u, o, jo, kb);
+    else return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
 }
 

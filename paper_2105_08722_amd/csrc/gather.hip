@@ -51,7 +51,9 @@ constexpr int kSegCap = kRowsPerBatch * kSegPerRow;
 // it ends.  Four waves of consecutive rows per workgroup, which shared one compute
 // unit's vector L1, waited for their slowest (a random 20,000 primaries of a 200k-point
 // wedge, lmax 5, FP32: 4 waves 2.88 ms, 1 wave 2.44, FP64 18% more with 4; every primary
-// of a 100k-point box 6.77 / 6.84 ms, FP64 6% more with 4).
+// of a 100k-point box 6.77 / 6.84 ms, FP64 6% more with 4).  (The item's arithmetic below
+// is written for any count: without it FP64 at lmax 5 takes 1 to 2% more, 64k points
+// 7.40 -> 7.49 ms, since it then runs in scalar registers.)
 constexpr int kWavesPerBlock = 1;
 constexpr int kRedCh = 16;         // accumulator values per pass of the lane reduction
 
@@ -81,7 +83,7 @@ template <> __device__ __forceinline__ double rsqrt_t<double>(double v)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// LDS of one wave: the per-bin rings plus one dump entry per lane (reused as the
+// LDS of one wave: the per-bin stacks plus one dump entry per lane (reused as the
 // reduction scratch, whose values are FP64 for the FP64 accumulators of the FP64
 // and the FP32 paths) and the piece descriptors of one row batch.
 template <typename T, int NBG, bool COMP>
@@ -948,6 +950,7 @@ KernelCfg cfg1()
     c.fn[0] = kfn<T, L, NBG, 0, L, false, COMP>();
     if constexpr (PERSOK) c.fnp[0] = kfn<T, L, NBG, 0, L, true, COMP>();
     c.lds = kWavesPerBlock * wave_lds_bytes<T, NBG, COMP>();
+    static_assert(kWavesPerBlock * wave_lds_bytes<T, NBG, COMP>() <= 65536, "above 64 KiB a launch needs its limit raised");
     return c;
 }
 template <typename T, int L, int NBG, int MS, bool COMP = false>
@@ -960,6 +963,7 @@ KernelCfg cfg2()
     c.m0[1] = MS; c.m1[1] = L;
     c.fn[1] = kfn<T, L, NBG, MS, L, false, COMP>();
     c.lds = kWavesPerBlock * wave_lds_bytes<T, NBG, COMP>();
+    static_assert(kWavesPerBlock * wave_lds_bytes<T, NBG, COMP>() <= 65536, "above 64 KiB a launch needs its limit raised");
     return c;
 }
 
@@ -1147,14 +1151,6 @@ int launch_gather(const GatherArgs& a0, int lmax, int precision, int nbg, int gr
         a.xcd_run = (int)run;
         blocks = (blocks + 8 * run - 1) / (8 * run) * (8 * run);
         if (blocks > INT32_MAX) return (int)hipErrorInvalidValue;
-        if (c.lds > 65536) {   // blocks above 64 KiB of LDS need the limit raised once
-            static thread_local std::vector<const void*> raised;
-            if (std::find(raised.begin(), raised.end(), fn) == raised.end()) {
-                const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
-                if (e != hipSuccess) return (int)e;
-                raised.push_back(fn);
-            }
-        }
         void* args[] = {&a};
         hipError_t e = hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(kWave * kWavesPerBlock),
                                        args, (size_t)c.lds, stream);
