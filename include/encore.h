@@ -298,7 +298,7 @@ int encore_autotune(encore_ctx* ctx, const double* pos, const double* w, int64_t
  * host; the grid is built beforehand), but the call makes no device allocation and
  * frees nothing: the coupling tables, the primary list, the per-slice
  * coefficients and partial sums, the job's sums and zeta all live in one static
- * scratch array of 256 MiB per device (held from the first encore_create on that
+ * scratch array of 257 MiB per device (held from the first encore_create on that
  * device until the process ends), and slices are sized to fit it.
  *  - Errors: ESIZE (with the bytes needed) when one slice of at least one coupling
  *    split no longer fits, e.g. N = 6 at lmax 4 with many bins.

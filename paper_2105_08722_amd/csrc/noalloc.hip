@@ -26,7 +26,12 @@ namespace encore {
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)256 << 20;   // 256 MiB per device
+// 256 MiB per device for what a call's sizes ask for, and room for the counters, queues and
+// job packs that every call carries on top (a call within 16 KiB of the limit was refused
+// when the pair counters grew from 64 bytes to kPairBytes).
+constexpr size_t kScratchFixed = (size_t)1 << 20;
+constexpr size_t kScratchBytes = ((size_t)256 << 20) + kScratchFixed;
+static_assert(kPairBytes + kQueueBytes + ((size_t)400 << 10) <= kScratchFixed, "400 KB: the 6PCF's packs at lmax 3");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
