@@ -439,7 +439,7 @@ def main():
     nbg = tuned["bins_per_item"] if tuned else 2
     roofline = {"bound": "alu", "achieved": achieved, "peak": PEAK_ALU_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_ALU_TFLOPS, "traffic": gather_traffic(pairs),
-                "kernel": "k_gather<float,5,%d,0,5,true,false> (harmonic-coefficient gather)" % nbg,
+                "kernel": "k_gather (harmonic-coefficient gather), lmax %d, %d bins per item" % (L, nbg),
                 "launch_ms": g_ms, "pairs_per_launch": pairs,
                 "flops_per_pair": gather_flops_per_pair(L)}
 

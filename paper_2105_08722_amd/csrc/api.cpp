@@ -138,7 +138,9 @@ int check_grids(const encore_grid* const* grids, int njobs, const encore_ctx* ct
 }
 
 // points per r_max^3 (averaged over the parts) from which encore_npcf_splits keeps
-// the data part of a~: measured break-even between 2,000 (0.95x) and 16,000 (1.09x)
+// the data part of a~: measured break-even (FP64) between 1,500 (4 parts of 250k points,
+// 4PCF lmax 5; 4 of 100k, 3PCF lmax 10 at 1,800) and 5,000 (2 parts of 60k); at 6,000 the
+// six job shapes measured gain 1 to 11%, at 3,000 two lose 2%
 constexpr double kSplitCacheDensity = 6000.0;
 
 }  // namespace

