@@ -100,12 +100,12 @@ __global__ void __launch_bounds__(kBlock) k_couple(CoupleArgs a, int ptile)
 // b3 > b2: about one product per output and primary instead of k_couple's three.
 // TI: the coefficients' type, TC: that of the products.  TILED (10 bins): the sums over a
 // tile of primaries are added to the FP64 sums, so that a split's thousands of terms are
-// not rounded one by one at the size of their sum; otherwise the terms are added to
-// the FP64 sums directly, over splits shorter than k_couple's.  Bound by FP64 issue
-// and the LDS reads alike at b1 = 0 (17 reads of 16 bytes for 104 multiply-adds).  With
-// the products as multiply-adds into the sums, and several b1 per launch, 10 bins at
-// lmax 5 over 60k primaries take 2.96 ms in FP64 (3.53 with products, then sums; 2.53
-// without tiles, whose sums round 2 to 3 times as much).
+// not rounded one by one at the size of their sum; otherwise the terms are added to the
+// FP64 sums directly, over splits as couple_split_rows cuts them.  Bound by FP64 issue and
+// the LDS reads alike at b1 = 0 (17 reads of 16 bytes for 104 multiply-adds).  With the
+// products as multiply-adds into the sums, and several b1 per launch, 10 bins at lmax 5
+// over 60k primaries take 2.96 ms in FP64 (3.53 with products, then sums; 2.53 without
+// tiles, whose sums are rounded 2 to 3 times as far).
 constexpr int kNB4 = 10;
 constexpr int kNB4Max = 12;   // its 55 FP64 sums and 2 x 12 coefficients per thread fit the registers
 __host__ __device__ constexpr int pair_count(int nr) { return (nr - 1) * (nr - 2) / 2; }   // b1 < b2 < b3 of nr bins
@@ -319,11 +319,12 @@ int launch4(const CoupleArgs& a, hipStream_t stream)
 // apart at 10 bins (4PCF lmax 5, 60k primaries, ms: FP64 {8..10} in one launch 3.08, {10}
 // alone 2.96; FP32 2.30, 2.07).  Other counts, with one set of sums, take one launch (8
 // bins 1.45, in two launches 1.59; FP32 path, 4k primaries, lmax 3, 9 bins 0.081, 0.104).
-int launch4_tiled(const CoupleArgs& a, hipStream_t stream)   // FP64, 10 bins
+template <typename T>
+int launch4_tiled(const CoupleArgs& a, hipStream_t stream)   // 10 bins
 {
-    int rc = launch4<double, double, true, kNB4, kNB4>(a, stream);
-    if (rc == (int)hipSuccess) rc = launch4<double, double, true, 8, 9>(a, stream);
-    return rc != (int)hipSuccess ? rc : launch4<double, double, true, 3, 7>(a, stream);
+    int rc = launch4<T, T, true, kNB4, kNB4>(a, stream);
+    if (rc == (int)hipSuccess) rc = launch4<T, T, true, 8, 9>(a, stream);
+    return rc != (int)hipSuccess ? rc : launch4<T, T, true, 3, 7>(a, stream);
 }
 template <typename TI>
 int launch4_fp64(const CoupleArgs& a, hipStream_t stream)    // other bin counts
@@ -331,26 +332,20 @@ int launch4_fp64(const CoupleArgs& a, hipStream_t stream)    // other bin counts
     return a.nbins > kNB4 ? launch4<TI, double, false, 3, kNB4Max>(a, stream)
                           : launch4<TI, double, false, 3, kNB4 - 1>(a, stream);
 }
-int launch4_fp32(const CoupleArgs& a, hipStream_t stream)
-{
-    int rc = launch4<float, float, true, kNB4, kNB4>(a, stream);
-    if (rc == (int)hipSuccess) rc = launch4<float, float, true, 8, 9>(a, stream);
-    return rc != (int)hipSuccess ? rc : launch4<float, float, true, 3, 7>(a, stream);
-}
 
 int launch_couple(const CoupleArgs& a, int precision, hipStream_t stream)
 {
     if (a.nk > kMaxK) return (int)hipErrorInvalidValue;
     if (a.nsplit == 0 || a.ntuple == 0) return (int)hipSuccess;
     if (use_couple4(a.nk, a.nbins, a.ntuple, a.nB)) {
-        if (precision == 0)
-            return a.nbins == kNB4 ? launch4_tiled(a, stream) : launch4_fp64<double>(a, stream);
-        // the FP32 products of 10 bins are summed in FP32 over a tile of primaries (2.07 ms
-        // at lmax 5 over 60k primaries, 2.96 for FP64 products and sums); at
-        // other bin counts, where k_couple added each FP32 product to an FP64 sum, the
-        // products are formed in FP64 too: a conversion and an addition in FP64 for each
-        // FP32 product would issue as long as the two FP64 multiply-adds
-        return a.nbins == kNB4 ? launch4_fp32(a, stream) : launch4_fp64<float>(a, stream);
+        // The FP32 products of 10 bins are summed in FP32 over a tile of primaries (2.07 ms
+        // at lmax 5 over 60k primaries, 2.96 for FP64 products and sums).  At other bin
+        // counts, where k_couple added each FP32 product to an FP64 sum, the products are
+        // formed in FP64 too: a conversion and an addition in FP64 for each FP32 product
+        // would issue as long as the two FP64 multiply-adds.
+        if (a.nbins == kNB4)
+            return precision == 0 ? launch4_tiled<double>(a, stream) : launch4_tiled<float>(a, stream);
+        return precision == 0 ? launch4_fp64<double>(a, stream) : launch4_fp64<float>(a, stream);
     }
     const int64_t nthreads = (int64_t)a.ntuple * a.nB;
     const int64_t nblk = (nthreads + kBlock - 1) / kBlock;

@@ -17,12 +17,12 @@
 //   k_lu_gemm   updates the next 64 columns (FP64 matrix cores); then the second 64
 //               columns the same way, their rows updated by the first 64's before U12,
 //   k_lu_gemm   updates the trailing matrix with all 128,
-// and k_lu_back substitutes back.  B with R_0 = 0 or a zero pivot get NaN and are
-// counted.
+// and k_lu_back substitutes back; k_edge_small solves systems of up to 32 multiplets
+// whole.  B with R_0 = 0 or a zero pivot get NaN and are counted.
 //
-// Measured, 10 radial bins: 6PCF lmax 3 (2,212 multiplets, 252 systems) 392 -> 84 ms a
-// call, matrix build 85 -> 18 ms, solve 307 -> 66 ms of which the trailing updates 41
-// ms (43 TFLOP/s; the FP64 16 x 16 x 4 instructions alone reach 48); 5PCF lmax 4 (585 x
+// Measured, 10 radial bins: 6PCF lmax 3 (2,212 multiplets, 252 systems) 392 -> 87 ms a
+// call, matrix build 85 -> 18 ms, solve 307 -> 68 ms of which the trailing updates 43
+// ms (41 TFLOP/s; the FP64 16 x 16 x 4 instructions alone reach 48); 5PCF lmax 4 (585 x
 // 210) 14.5 -> 4.2 ms, of which the panels 1.5 ms.  Before, one workgroup per system
 // did every step, with panels of 32 columns eliminated in global memory.
 #include <hip/hip_runtime.h>
@@ -560,14 +560,14 @@ __global__ void __launch_bounds__(256) k_lu_rows(LuArgs u, int o, int jo, int kb
 // A[r][c] -= sum_{k < K} P[k][r] A[o + k][c] for rows r0 <= r < r1 and columns
 // c0 <= c < c1: tiles of TM x TN by four waves, the operands of 16 k staged in LDS while
 // the next 16 are on their way to registers, 16 x 16 x 4 FP64 matrix instructions.  The
-// products are summed by themselves and then subtracted, here and in the steps below 64
-// columns: added to A one by one (with A as the accumulator), each was rounded at
-// the size of A, and systems of 65 to 585 multiplets were solved 1.5 to 10 times less
-// exactly (6PCF lmax 3, 252 systems: 86.0 ms, 84.3 with A as the accumulator, 100 with A
-// read by a wave all at once at the end).  The LDS rows are 16 doubles longer than a multiple of 32,
-// so that the two k rows a half-wave reads lie on different halves of the banks.  Tiles
-// at the edge read L and U past the panel's rows and columns: those products land in
-// rows and columns that are not stored.
+// products are summed by themselves and then subtracted, here and in the panels and U12:
+// with A as the accumulator each was rounded at the size of A, and systems of 65 to 585
+// multiplets were solved 1.5 to 10 times less exactly (6PCF lmax 3, 252 systems: 86.0 ms,
+// 84.3 with A as the accumulator, 100 with a wave's part of A read at once at the end).
+// The LDS rows are 16 doubles longer than a multiple of 32, so that the two k rows a
+// half-wave reads lie on different halves of the banks.  Tiles at the edge read L and U
+// past the panel's rows and columns: those products land in rows and columns that are
+// not stored.
 constexpr int kGemmM = 128, kGemmK = 16;
 template <int TM, int TN>
 __global__ void __launch_bounds__(256, 2) k_lu_gemm(LuArgs u, int o, int K, int r0, int r1, int c0, int c1, int tx,
