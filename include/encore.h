@@ -279,7 +279,9 @@ int encore_mfma_plan_stats(int npcf, int lmax, int nbins, uint32_t flags, int64_
  * grid of a pass over every point, persistent or one wave per item), for every compiled
  * bins-per-work-item value of the gather.  The fastest (d, s) becomes the cell
  * shape of later grids built on ctx; the fastest bins-per-item value is used by
- * later calls with the same lmax, gather precision and nbins.  The default shape
+ * later calls with the same lmax, gather precision and nbins (not by plain FP32 gathers
+ * over a primary subset of 300,000 points or more at lmax <= 4, which take a wider value
+ * of their own: such primaries come in any order).  The default shape
  * and bins per item are kept unless the fastest is more than 2% faster on the
  * sample (sample timings of nearby shapes differ by about that much).  The choice changes
  * only the order of floating-point operations, never what is computed.
